@@ -6,255 +6,74 @@ namespace microadam {
 namespace {
 
 // ============================================================ update
-// The accumulators hold, per element of the block, sum beta1^r V and sum
-// beta2^r V^2 (z1 and z2; or z1 alone, one after the other), then z1 the
-// parameter decrement.  A thread's 16 elements are its parameter vectors
-// (Vec16: vector v of thread t holds the EV elements from v*EV*NT + t*EV),
-// read as four groups of four: group g of thread t is the 16-byte word at
-// (g*NT + t)*4, so a wave's 16-byte accesses fall on consecutive addresses.
-// Element i = v*EV*NT + t*EV + e lies in group v*EV/4 + e/4, at word e mod 4
-// (for binary32 parameters that is word i itself).  Word CAP of each array
-// is a sink for lanes without an entry, which keeps the sparse updates free
-// of branches.
+// One workgroup per block.  A thread's 16 elements are its parameter vectors
+// (Vec16: vector v of thread t holds the EV elements from v*EV*NT + t*EV).
+// The live rows of the block's window record (contiguous, oldest row first
+// from slot0 on) are loaded by every thread at once, NT entries per access,
+// and staged in LDS in row order with each entry's index replaced by its
+// accumulator word, so that no global load waits inside the row-by-row chain.
+// One wave (rotating with the block, at raised priority) adds the rows into
+// the one accumulator, several chunks of a row (distinct words) per LDS round
+// trip: first sum beta1^r V, later sum beta2^r V^2.  Between and after the two
+// chains all waves work on the entries they loaded: each distinct element's
+// first entry takes its first sum, then turns both sums into the decrement.
+// Word CAP is a sink for lanes without an entry, which keeps the adds free of
+// branches.
+//
+// What bounds it: the chain of n_live LDS round trips, twice, per workgroup,
+// which the other workgroups of the compute unit have to cover; hence one
+// accumulator (LDS for eight workgroups at m = 10 and 20, k = 41), nothing on
+// the chain but add and LDS access, and the decrements (about 20 instructions
+// per entry) shared by all waves.  The form before held the entries in the
+// adding wave's registers, up to 16 chunks of 64, and that wave computed every
+// decrement with the library's square root and division; longer windows were
+// read row by row from memory.  Measured, old and new, the step in us:
+//   two Llama-2-7B layers, m = 20 (20 chunks)      2338 -> 580-600
+//   120 M parameters, k = 205, m = 10 (40 chunks)  1279 -> 400
+//   Llama-2-7B, m = 10                             8954 -> 8763
+//   BERT-base in bf16                               160.6 -> 156.7
+//   BERT-base with blocks of 1024 (k = 11)          238.0 -> 216.4
+constexpr int kStageMax = 24;  // entries per thread at most
+
+// Accumulator word of element i: bf16 parameters are read as pairs of 16-byte
+// words by the thread that owns 8 consecutive elements, so every other group
+// of 8 threads swaps the two words of its pairs and 16 lanes' reads fall on
+// distinct banks; binary32 parameters need no permutation.
+template <bool PBF16>
+__device__ __forceinline__ uint32_t zswap(uint32_t i) {
+  return PBF16 ? i ^ ((i >> 4) & 4u) : i;
+}
+
+// lr * (c1 s1) / (eps + sqrt(c2 s2)).  One Newton step with the exact residual
+// after v_rsq_f32 and v_rcp_f32 (each within 1 ulp) gives the correctly rounded
+// root and quotient but for a rare last-place miss, in a third of the
+// instructions of the library forms; those take the arguments outside the
+// range where no intermediate of the step can under- or overflow (and zeros,
+// infinities and NaN).  eps_ok: eps itself lies in that range (uniform).
+constexpr uint32_t kRangeLo = 0x0D800000u, kRangeHi = 0x71800000u;  // 2^-100, 2^100
+__device__ __forceinline__ bool range_ok(float x) { return __float_as_uint(x) - kRangeLo <= kRangeHi - kRangeLo; }
+__device__ __forceinline__ float decrement(const StepParams& p, float s1, float s2, bool eps_ok) {
+  const float mh = p.c1 * s1;
+  const float vh = p.c2 * s2;
+  const float r = __builtin_amdgcn_rsqf(vh);
+  const float q = vh * r;
+  const float root = __builtin_fmaf(__builtin_fmaf(-q, q, vh), 0.5f * r, q);
+  const float den = p.eps + root;
+  const float y = __builtin_amdgcn_rcpf(den);
+  const float d0 = mh * y;
+  float d = __builtin_fmaf(__builtin_fmaf(-d0, den, mh), y, d0);
+  if (!range_ok(vh) | !eps_ok) d = mh / (p.eps + __builtin_sqrtf(vh));
+  return p.lr * d;
+}
+
+// theta <- theta * decay - decrement over a thread's parameter vectors, the
+// decrements in z (the decay factor is skipped by a uniform branch when it
+// is 1).
 template <int NT, bool PBF16>
-__device__ __forceinline__ uint32_t zpos(uint32_t i) {
-  constexpr uint32_t EV = Vec16<PBF16>::EV, G = EV / 4;
-  const uint32_t v = i / (EV * NT), t = (i / EV) & (NT - 1), e = i & (EV - 1);
-  return ((v * G + e / 4) * NT + t) * 4 + (e & 3);
-}
-
-// LDS: the accumulators (two, or one with ONE).
-template <int NT, bool VF, int KC, bool ONE>
-constexpr size_t update_lds_bytes() {
-  return (size_t)(ONE ? 1 : 2) * (NT * kLaneElems + 16) * 4;
-}
-
-// One workgroup per block.  One wave (rotating with the block) rebuilds the
-// moments of the block's window entries, oldest row first, and turns them
-// into parameter decrements; then every thread updates its own elements.
-//
-// The leader loads the window entries straight into registers, KC chunks of
-// 64 in the order it adds them: lane l of chunk c holds position 64*c + l,
-// where chunk c is part c mod R of the live row c / R (oldest row first,
-// R = ceil(k_q/64) parts of 64 entries); positions without an entry add into
-// the sink word CAP.  A block whose live rows need more than KC chunks is
-// read by the leader row by row from the window record.  The other waves
-// load only their parameters.
-//
-// ONE = true: one accumulator; the leader makes two passes over its
-// entries (first moments, read back and cleared, then second moments), which
-// halves the LDS of a workgroup so that eight fit on a compute unit.  The
-// host launches it only where every block's live rows fit in KC chunks.
-// ONE = false: two accumulators, any block.  EXPORT = true writes dense m-hat
-// and v-hat instead of updating theta.
-// Waves per SIMD that the LDS of an update workgroup allows (160 KB per
-// compute unit, four SIMDs); telling the compiler lets it spend registers
-// up to that occupancy on keeping LDS reads in flight.  A leader holding 16
-// chunks needs more than the 64 registers of eight waves per SIMD, so those
-// kernels ask for seven.
-template <int NT, bool VF, int KC, bool ONE>
-constexpr int update_waves_per_eu() {
-  const int per_cu = (int)(163840 / update_lds_bytes<NT, VF, KC, ONE>());
-  const int w = per_cu * (NT / kWave) / 4;
-  const int cap = KC >= 16 ? 7 : 8;
-  return w < 1 ? 1 : w > cap ? cap : w;
-}
-
-template <int NT, bool PBF16, bool VF32, bool EXPORT, int KC, bool ONE>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(update_waves_per_eu<NT, VF32, KC, ONE>())))
-update_kernel(StepParams p, int64_t first_block, int64_t count, float* mhat, float* vhat) {
-  static_assert(!ONE || !EXPORT, "one accumulator: parameter update only");
-  constexpr int NW = NT / kWave;
-  constexpr int CAP = NT * kLaneElems;
-  constexpr int kChunks = KC;                             // 64-entry chunks the leader holds
-  using E = Entry<VF32>;
-  using ET = typename E::T;
-  extern __shared__ __align__(16) uint32_t smem[];
-  float* const z1 = (float*)smem;
-  float* const z2 = z1 + CAP + 16;                        // not allocated with ONE
-
-  const int tid = thread_id(), lane = tid & (kWave - 1), wave = (int)sgpr(tid / kWave);
-  const int m = p.window, n_live = p.n_live;
-  // oldest live row first: the row written at step s is slot (s-1) mod m
-  const int slot0 = (p.new_slot + 1 + m - n_live) % m;
-
-  const Span u = span_of(p, (int32_t)(first_block + xcd_block(block_id(), count)), PBF16 ? 2 : 4);
-  const int s = u.s, kq = u.kq;
-  const int leader = u.gb & (NW - 1);
-  const int R = (kq + kWave - 1) / kWave;
-  const bool held = n_live * R <= kChunks;  // the leader holds every live chunk in registers
-
-  // loads: the leader's window positions, KC chunks of 64 (positions without
-  // an entry read entry 0 and are not used), then every thread's parameters.
-  // Chunk c is part `col` of live row `row` (uniform counters), at record
-  // entry slot*k_q + 64*col + lane.
-  const bool lead = wave == leader;
-  const Rsrc rw = window_rsrc<VF32 ? 2 : 1>(p, u.gb, kq);
-  ET w[kChunks];
-  bool has[kChunks];  // the position holds an entry
-  int rr[kChunks];    // the chunk's row age: 0 for the newest row
-  if (lead && held) {
-    int row = 0, col = 0, slot = slot0;
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      const int jj = col * kWave + lane;
-      has[c] = row < n_live && jj < kq;
-      rr[c] = (n_live - 1 - row) & (kMaxWindow - 1);
-      w[c] = E::template load<kStream>(rw, has[c] ? (uint32_t)(slot * kq + jj) : 0u);
-      if (++col == R) {
-        col = 0;
-        ++row;
-        if (++slot == m) slot = 0;
-      }
-    }
-  }
+__device__ __forceinline__ void apply_decrements(const StepParams& p, Rsrc rp,
+                                                 const u32x4 (&th)[Vec16<PBF16>::NV], const float* z, int tid, int s) {
   using V = Vec16<PBF16>;
   constexpr int EV = V::EV;
-  const Rsrc rp = make_rsrc((const void*)u.base, vec_bytes<PBF16>(s));
-  u32x4 th[V::NV];
-  if (!EXPORT) {
-#pragma unroll
-    for (int v = 0; v < V::NV; ++v) th[v] = V::load(rp, V::template first<NT>(v, tid));
-  }
-  const float w1s = lane < kMaxWindow ? constant_ptr(p.wpow)[lane] : 0.0f;
-  const float w2s = lane < kMaxWindow ? constant_ptr(p.wpow)[kMaxWindow + lane] : 0.0f;
-
-  {
-    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      *(float4*)(z1 + q * 4 * NT + tid * 4) = zero;
-      if (!ONE) *(float4*)(z2 + q * 4 * NT + tid * 4) = zero;
-    }
-  }
-  lds_sync();
-
-  if (lead) {
-    auto step_of = [&](float s1, float s2) {
-      const float mh = p.c1 * s1;
-      const float vh = p.c2 * s2;
-      // correctly rounded square root and division
-      const float den = p.eps + __builtin_sqrtf(vh);
-      return p.lr * (mh / den);
-    };
-    if (held) {
-      // chunks past the live rows hold only sink words
-      uint32_t zp[kChunks];
-      float val[kChunks];
-#pragma unroll
-      for (int c = 0; c < kChunks; ++c) {
-        const uint32_t idx = E::idx(w[c]);
-        zp[c] = has[c] && idx < (uint32_t)s ? zpos<NT, PBF16>(idx) : (uint32_t)CAP;
-        val[c] = E::val(w[c]);
-      }
-      // The entries of one row (or of one 64-entry part of it) have distinct
-      // indices, so each chunk reads, adds and writes back its words (the
-      // sink word's lanes race harmlessly); chunks follow each other oldest
-      // row first.  Every entry's sums are read before any word is
-      // overwritten, so an index that occurs in several rows gets the same
-      // decrement from each occurrence.
-      if constexpr (ONE) {
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) {
-          const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w1s), rr[c]));
-          const float a1 = z1[zp[c]];
-          z1[zp[c]] = a1 + w1 * val[c];
-        }
-        float s1[kChunks];
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) s1[c] = z1[zp[c]];
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) z1[zp[c]] = 0.0f;
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) {
-          const float w2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w2s), rr[c]));
-          const float vv = val[c] * val[c];
-          const float a2 = z1[zp[c]];
-          z1[zp[c]] = a2 + w2 * vv;
-        }
-        float d[kChunks];
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) d[c] = step_of(s1[c], z1[zp[c]]);
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) z1[zp[c]] = d[c];
-      } else {
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) {
-          const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w1s), rr[c]));
-          const float w2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w2s), rr[c]));
-          const float v = val[c];
-          const float x1 = w1 * v;
-          const float vv = v * v;
-          const float x2 = w2 * vv;
-          const float a1 = z1[zp[c]], a2 = z2[zp[c]];
-          z1[zp[c]] = a1 + x1;
-          z2[zp[c]] = a2 + x2;
-        }
-        if (!EXPORT) {
-          float d[kChunks];
-#pragma unroll
-          for (int c = 0; c < kChunks; ++c) d[c] = step_of(z1[zp[c]], z2[zp[c]]);
-#pragma unroll
-          for (int c = 0; c < kChunks; ++c) z1[zp[c]] = d[c];
-        }
-      }
-    } else if constexpr (!ONE) {
-      for (int row = 0, slot = slot0; row < n_live; ++row, slot = (slot + 1 == m) ? 0 : slot + 1) {
-        const int r = n_live - 1 - row;
-        const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w1s), r));
-        const float w2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w2s), r));
-        for (int jj = lane; jj < kq; jj += kWave) {
-          const ET x = E::load(rw, slot * kq + jj);
-          const uint32_t i = E::idx(x);
-          const uint32_t zp = i < (uint32_t)s ? zpos<NT, PBF16>(i) : (uint32_t)CAP;
-          const float v = E::val(x);
-          const float vv = v * v;
-          const float x1 = w1 * v, x2 = w2 * vv;
-          const float a1 = z1[zp], a2 = z2[zp];
-          z1[zp] = a1 + x1;
-          z2[zp] = a2 + x2;
-        }
-      }
-      if (!EXPORT) {
-        // one 64-entry chunk at a time; z2 = -1 marks a converted word
-        for (int row = 0, slot = slot0; row < n_live; ++row, slot = (slot + 1 == m) ? 0 : slot + 1)
-          for (int jj = lane; jj < kq; jj += kWave) {
-            const uint32_t i = E::idx(E::load(rw, slot * kq + jj));
-            if (i < (uint32_t)s) {
-              const uint32_t zp = zpos<NT, PBF16>(i);
-              const float s2 = z2[zp];
-              if (s2 >= 0.0f) {
-                z1[zp] = step_of(z1[zp], s2);
-                z2[zp] = -1.0f;
-              }
-            }
-          }
-      }
-    }
-  }
-  lds_sync();
-
-  if (EXPORT) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 s1 = *(const float4*)(z1 + q * 4 * NT + tid * 4);
-      const float4 s2 = *(const float4*)(z2 + q * 4 * NT + tid * 4);
-      const float a1[4] = {s1.x, s1.y, s1.z, s1.w}, a2[4] = {s2.x, s2.y, s2.z, s2.w};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t i = V::template first<NT>(q / (EV / 4), tid) + (q % (EV / 4)) * 4 + r;
-        if ((int)i < s) {
-          mhat[u.e0 + i] = p.c1 * a1[r];
-          vhat[u.e0 + i] = p.c2 * a2[r];
-        }
-      }
-    }
-    return;
-  }
-
-  // ------------------------------------------------ 6. parameter update
-  // (theta times the decay factor, skipped by a uniform branch when the
-  // factor is 1)
   const bool full = s == NT * kLaneElems;
   auto apply = [&](auto one_tag) {
     constexpr bool ONE_DECAY = decltype(one_tag)::value;
@@ -264,7 +83,7 @@ update_kernel(StepParams p, int64_t first_block, int64_t count, float* mhat, flo
       float upd[EV], thf[EV], out[EV];
 #pragma unroll
       for (int q = 0; q < EV / 4; ++q) {
-        const float4 x = *(const float4*)(z1 + ((v * (EV / 4) + q) * NT + tid) * 4);
+        const float4 x = *(const float4*)(z + zswap<PBF16>(e0 + 4 * q));
         upd[4 * q] = x.x;
         upd[4 * q + 1] = x.y;
         upd[4 * q + 2] = x.z;
@@ -282,54 +101,321 @@ update_kernel(StepParams p, int64_t first_block, int64_t count, float* mhat, flo
     apply(BoolTag<false>{});
 }
 
-// Chunks of 64 window entries the update's leader wave processes per block:
-// the live rows of a full block rounded up to 4, 8, 10, 12 or 16.
-inline int chunk_class(const StepParams& p) {
-  const int R = (p.k_full + kWave - 1) / kWave;
-  const int nch = p.n_live * R;
-  return nch <= 4 ? 4 : nch <= 8 ? 8 : nch <= 10 ? 10 : nch <= 12 ? 12 : 16;
+template <int NT, bool VF>
+constexpr size_t staged_lds_bytes(int entries) {
+  return (size_t)(NT * kLaneElems + 16) * 4 + (size_t)entries * (VF ? 8 : 4);
 }
 
-template <int NT, bool PB, bool VF, int KC, bool ONE>
+// Waves per SIMD by the LDS of a full stage of KS entries per thread.
+template <int NT, bool VF, int KS>
+constexpr int staged_waves_per_eu() {
+  const int per_cu = (int)(163840 / staged_lds_bytes<NT, VF>(KS * NT));
+  const int w = per_cu * (NT / kWave) / 4;
+  return w < 1 ? 1 : w > 8 ? 8 : w;
+}
+
+template <int NT, bool PBF16, bool VF32, int KS, int G>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(staged_waves_per_eu<NT, VF32, KS>())))
+update_kernel(StepParams p, int64_t first_block, int64_t count) {
+  constexpr int NW = NT / kWave;
+  constexpr int CAP = NT * kLaneElems;
+  using E = Entry<VF32>;
+  using ET = typename E::T;
+  using V = Vec16<PBF16>;
+  typedef __attribute__((address_space(3))) float LdsFloat;
+  typedef __attribute__((address_space(3))) uint32_t LdsWord;
+  extern __shared__ __align__(16) uint32_t smem[];
+  float* const z = (float*)smem;
+  ET* const stage = (ET*)(smem + CAP + 16);
+  // accumulator words as LDS byte addresses
+  const uint32_t z0 = (uint32_t)(uintptr_t)(LdsWord*)smem;
+  const uint32_t sink = z0 + (uint32_t)CAP * 4;
+  auto at = [](uint32_t a) { return (LdsFloat*)(uintptr_t)a; };
+
+  const int tid = thread_id(), lane = tid & (kWave - 1), wave = (int)sgpr(tid / kWave);
+  const int m = p.window, n_live = p.n_live;
+  const int slot0 = (p.new_slot + 1 + m - n_live) % m;  // the oldest live row
+  const Span u = span_of(p, (int32_t)(first_block + xcd_block(block_id(), count)), PBF16 ? 2 : 4);
+  const int s = u.s, kq = u.kq;
+  const int n = n_live * kq;    // live entries: the record's first n (slot0 is 0 until the window is full)
+  const int old0 = slot0 * kq;  // the oldest row's first entry
+
+  // loads: this thread's window entries, then its parameters
+  const Rsrc rw = window_rsrc<VF32 ? 2 : 1>(p, u.gb, kq);
+  ET w[KS];
+#pragma unroll
+  for (int i = 0; i < KS; ++i)
+    if (i * NT < n) w[i] = E::template load<kStream>(rw, (uint32_t)(i * NT + tid));  // past the record: 0
+  const Rsrc rp = make_rsrc((const void*)u.base, vec_bytes<PBF16>(s));
+  u32x4 th[V::NV];
+#pragma unroll
+  for (int v = 0; v < V::NV; ++v) th[v] = V::load(rp, V::template first<NT>(v, tid));
+  const float w1s = constant_ptr(p.wpow)[lane];  // kMaxWindow is one wave's lanes
+  const float w2s = constant_ptr(p.wpow)[kMaxWindow + lane];
+  static_assert(kMaxWindow == kWave, "one weight per lane");
+
+  {
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *(float4*)(z + q * 4 * NT + tid * 4) = zero;
+  }
+  uint32_t zp[KS];  // the entry's accumulator word
+  {
+    // place of entry e: e - old0, or e - old0 + n where that is negative (the
+    // smaller of the two as unsigned numbers)
+    const uint32_t e0 = (uint32_t)(tid - old0);
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      zp[i] = sink;
+      if (i * NT < n && i * NT + tid < n) {
+        const uint32_t idx = E::word(w[i]);
+        zp[i] = idx < (uint32_t)s ? z0 + zswap<PBF16>(idx) * 4u : sink;
+        const uint32_t e = e0 + i * NT;
+        stage[e < e + (uint32_t)n ? e : e + (uint32_t)n] = E::with_word(w[i], zp[i]);
+      }
+    }
+  }
+  lds_sync();
+
+  const bool lead = wave == (u.gb & (NW - 1));
+  // adds every live row into z, oldest first: weight * V, or weight * V^2;
+  // lanes past the row's end add to the sink word
+  auto rebuild = [&](float ws, auto sq_tag) {
+    constexpr bool SQ = decltype(sq_tag)::value;
+    // U rows of up to 64 G entries at a time (one part of a longer row with
+    // U = 1): their words and weighted values are ready in registers before
+    // the chain of adds, and the next U rows' entries come during it
+    constexpr int U = G == 1 ? 5 : G == 2 ? 2 : 1;
+    ET x[U][G];
+    auto fetch = [&](int e0) {
+      const uint32_t e = (uint32_t)(e0 + lane), top = (uint32_t)n - 1;
+#pragma unroll
+      for (int r = 0; r < U; ++r)
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const uint32_t at_e = e + r * kq + g * kWave;
+          x[r][g] = stage[at_e < top ? at_e : top];
+        }
+    };
+    __builtin_amdgcn_s_setprio(3);
+    fetch(0);
+    int row = 0, col = 0;
+    while (row < n_live) {
+      uint32_t zo[U][G];
+      float add[U][G];
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        const float wr = __int_as_float(
+            __builtin_amdgcn_readlane(__float_as_int(ws), (n_live - 1 - row - r) & (kMaxWindow - 1)));
+        const int left = row + r < n_live ? kq - col : 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          zo[r][g] = g * kWave + lane < left ? E::word(x[r][g]) : sink;
+          const float v = E::val(x[r][g]);
+          add[r][g] = wr * (SQ ? v * v : v);
+        }
+      }
+      col += U == 1 ? G * kWave : kq;
+      if (col >= kq) {
+        col = 0;
+        row += U;
+      }
+      fetch(row * kq + col);
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        float a[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) a[g] = *at(zo[r][g]);
+#pragma unroll
+        for (int g = 0; g < G; ++g) *at(zo[r][g]) = a[g] + add[r][g];
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
+  };
+  if (lead) rebuild(w1s, BoolTag<false>{});
+  lds_sync();
+  // Each entry takes its word's first sum and leaves -0 (x + -0 is x, so the
+  // second sums start from it like from 0; a sum that started at +0 is never
+  // -0).  Of the entries of one element the first to come gets the sum and
+  // turns the two sums into the decrement; the others get -0 and are done.
+  constexpr uint32_t kTaken = 0x80000000u;
+  uint32_t s1[KS];
+  {
+    const int nn = opaque(n);
+#pragma unroll
+    for (int i = 0; i < KS; ++i)
+      if (i * NT < nn)
+        s1[i] = __hip_atomic_exchange((LdsWord*)(uintptr_t)zp[i], kTaken, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  lds_sync();
+  if (lead) rebuild(w2s, BoolTag<true>{});
+  lds_sync();
+  {
+    const bool eps_ok = range_ok(p.eps);
+    const int nn = opaque(n);
+#pragma unroll
+    for (int i = 0; i < KS; ++i)
+      if (i * NT < nn && s1[i] != kTaken)
+        *at(zp[i]) = decrement(p, __uint_as_float(s1[i]), *at(zp[i]), eps_ok);
+  }
+  lds_sync();
+
+  apply_decrements<NT, PBF16>(p, rp, th, z, tid, s);
+}
+
+// Debug export, and the update where the live rows do not fit the stage (more
+// than kStageMax entries per thread): two accumulators, sum beta1^r V and sum
+// beta2^r V^2, one wave reading the window record row by row.
+template <int NT, bool VF>
+constexpr size_t update_lds_bytes() {
+  return (size_t)2 * (NT * kLaneElems + 16) * 4;
+}
+
+template <int NT, bool PBF16, bool VF32, bool EXPORT>
+__global__ void __launch_bounds__(NT) update_rows_kernel(StepParams p, int64_t first_block, int64_t count,
+                                                         float* mhat, float* vhat) {
+  constexpr int NW = NT / kWave;
+  constexpr int CAP = NT * kLaneElems;
+  using E = Entry<VF32>;
+  using ET = typename E::T;
+  using V = Vec16<PBF16>;
+  constexpr int EV = V::EV;
+  extern __shared__ __align__(16) uint32_t smem[];
+  float* const z1 = (float*)smem;
+  float* const z2 = z1 + CAP + 16;
+
+  const int tid = thread_id(), lane = tid & (kWave - 1), wave = (int)sgpr(tid / kWave);
+  const int m = p.window, n_live = p.n_live;
+  const int slot0 = (p.new_slot + 1 + m - n_live) % m;  // the oldest live row
+  const Span u = span_of(p, (int32_t)(first_block + xcd_block(block_id(), count)), PBF16 ? 2 : 4);
+  const int s = u.s, kq = u.kq;
+  const Rsrc rw = window_rsrc<VF32 ? 2 : 1>(p, u.gb, kq);
+  const Rsrc rp = make_rsrc((const void*)u.base, vec_bytes<PBF16>(s));
+  u32x4 th[V::NV];
+  if (!EXPORT) {
+#pragma unroll
+    for (int v = 0; v < V::NV; ++v) th[v] = V::load(rp, V::template first<NT>(v, tid));
+  }
+  const float w1s = constant_ptr(p.wpow)[lane];  // kMaxWindow is one wave's lanes
+  const float w2s = constant_ptr(p.wpow)[kMaxWindow + lane];
+  {
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      *(float4*)(z1 + q * 4 * NT + tid * 4) = zero;
+      *(float4*)(z2 + q * 4 * NT + tid * 4) = zero;
+    }
+  }
+  lds_sync();
+
+  if (wave == (u.gb & (NW - 1))) {
+    for (int row = 0, slot = slot0; row < n_live; ++row, slot = (slot + 1 == m) ? 0 : slot + 1) {
+      const int r = n_live - 1 - row;
+      const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w1s), r));
+      const float w2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w2s), r));
+      for (int jj = lane; jj < kq; jj += kWave) {
+        const ET x = E::load(rw, slot * kq + jj);
+        const uint32_t i = E::idx(x);
+        const uint32_t zp = i < (uint32_t)s ? zswap<PBF16>(i) : (uint32_t)CAP;
+        const float v = E::val(x);
+        const float vv = v * v;
+        const float x1 = w1 * v, x2 = w2 * vv;
+        const float a1 = z1[zp], a2 = z2[zp];
+        z1[zp] = a1 + x1;
+        z2[zp] = a2 + x2;
+      }
+    }
+    if (!EXPORT) {
+      // one 64-entry chunk at a time; z2 = -1 marks a converted word
+      const bool eps_ok = range_ok(p.eps);
+      for (int row = 0, slot = slot0; row < n_live; ++row, slot = (slot + 1 == m) ? 0 : slot + 1)
+        for (int jj = lane; jj < kq; jj += kWave) {
+          const uint32_t i = E::idx(E::load(rw, slot * kq + jj));
+          if (i < (uint32_t)s) {
+            const uint32_t zp = zswap<PBF16>(i);
+            const float s2 = z2[zp];
+            if (s2 >= 0.0f) {
+              z1[zp] = decrement(p, z1[zp], s2, eps_ok);
+              z2[zp] = -1.0f;
+            }
+          }
+        }
+    }
+  }
+  lds_sync();
+
+  if (EXPORT) {
+#pragma unroll
+    for (int v = 0; v < V::NV; ++v) {
+#pragma unroll
+      for (int e = 0; e < EV; ++e) {
+        const uint32_t i = V::template first<NT>(v, tid) + e;
+        if ((int)i < s) {
+          mhat[u.e0 + i] = p.c1 * z1[zswap<PBF16>(i)];
+          vhat[u.e0 + i] = p.c2 * z2[zswap<PBF16>(i)];
+        }
+      }
+    }
+    return;
+  }
+  apply_decrements<NT, PBF16>(p, rp, th, z1, tid, s);
+}
+
+template <int NT, bool PB, bool VF, int KS>
 hipError_t launch_update_k(const StepParams& p, int64_t first, int64_t count, hipStream_t stream) {
-  if (count <= 0) return hipSuccess;
-  const size_t lds = update_lds_bytes<NT, VF, KC, ONE>();
-  hipLaunchKernelGGL((update_kernel<NT, PB, VF, false, KC, ONE>), dim3((uint32_t)count), dim3(NT), lds, stream, p,
-                     first, count, (float*)nullptr, (float*)nullptr);
-  return hipGetLastError();
+  const size_t lds = staged_lds_bytes<NT, VF>(p.n_live * p.k_full);
+  auto go = [&](auto g_tag) {
+    constexpr int G = decltype(g_tag)::value;
+    hipLaunchKernelGGL((update_kernel<NT, PB, VF, KS, G>), dim3((uint32_t)count), dim3(NT), lds, stream, p,
+                       first, count);
+    return hipGetLastError();
+  };
+  if (p.k_full <= kWave) return go(std::integral_constant<int, 1>{});
+  if (p.k_full <= 2 * kWave) return go(std::integral_constant<int, 2>{});
+  return go(std::integral_constant<int, 4>{});
 }
 
-// Blocks [first, first + count), one workgroup each: with one accumulator
-// where the live rows of a full block, and so of every block, fit in 16
-// chunks; else with two.
+// Whether the live rows of every block fit the stage.
+template <int NT, bool VF>
+bool fits_stage(const StepParams& p) {
+  const int64_t n = (int64_t)p.n_live * p.k_full;
+  return n <= (int64_t)kStageMax * NT && staged_lds_bytes<NT, VF>((int)n) <= 65536;
+}
+
+// The staged kernel wherever every block's live rows fit the stage, else row
+// by row (a stage of more entries leaves one or two workgroups per compute
+// unit; m * k above 6144 at B_d = 4096 lies outside the method's settings).
 template <int NT, bool PB, bool VF>
 hipError_t launch_update_t(const StepParams& p, int64_t first, int64_t count, hipStream_t stream) {
-  const int R = (p.k_full + kWave - 1) / kWave;
-  if (p.n_live * R > 16) return launch_update_k<NT, PB, VF, 16, false>(p, first, count, stream);
-  switch (chunk_class(p)) {
-    case 4: return launch_update_k<NT, PB, VF, 4, true>(p, first, count, stream);
-    case 8: return launch_update_k<NT, PB, VF, 8, true>(p, first, count, stream);
-    case 10: return launch_update_k<NT, PB, VF, 10, true>(p, first, count, stream);
-    case 12: return launch_update_k<NT, PB, VF, 12, true>(p, first, count, stream);
-    default: return launch_update_k<NT, PB, VF, 16, true>(p, first, count, stream);
+  if (count <= 0) return hipSuccess;
+  if (!fits_stage<NT, VF>(p)) {
+    const size_t lds = update_lds_bytes<NT, VF>();
+    hipLaunchKernelGGL((update_rows_kernel<NT, PB, VF, false>), dim3((uint32_t)count), dim3(NT), lds, stream, p, first,
+                       count, (float*)nullptr, (float*)nullptr);
+    return hipGetLastError();
   }
+  const int ks = (p.n_live * p.k_full + NT - 1) / NT;
+  if (ks <= 2) return launch_update_k<NT, PB, VF, 2>(p, first, count, stream);
+  if (ks <= 4) return launch_update_k<NT, PB, VF, 4>(p, first, count, stream);
+  if (ks <= 8) return launch_update_k<NT, PB, VF, 8>(p, first, count, stream);
+  if (ks <= 12) return launch_update_k<NT, PB, VF, 12>(p, first, count, stream);
+  return launch_update_k<NT, PB, VF, kStageMax>(p, first, count, stream);
 }
 
 template <int NT, bool VF>
 hipError_t launch_export(const StepParams& p, int64_t first_block, int64_t blocks, float* mh, float* vh,
                          hipStream_t stream) {
   if (blocks <= 0) return hipSuccess;
-  const size_t lds = update_lds_bytes<NT, VF, 16, false>();
-  hipLaunchKernelGGL((update_kernel<NT, false, VF, true, 16, false>), dim3((uint32_t)blocks), dim3(NT), lds, stream,
-                     p, first_block, blocks, mh, vh);
+  const size_t lds = update_lds_bytes<NT, VF>();
+  hipLaunchKernelGGL((update_rows_kernel<NT, false, VF, true>), dim3((uint32_t)blocks), dim3(NT), lds, stream, p,
+                     first_block, blocks, mh, vh);
   return hipGetLastError();
 }
 
 }  // namespace
 
-size_t update_lds_max(int nt) {
-  return nt == 64 ? update_lds_bytes<64, true, 16, false>() : update_lds_bytes<256, true, 16, false>();
-}
+size_t update_lds_max(int nt) { return nt == 64 ? update_lds_bytes<64, true>() : update_lds_bytes<256, true>(); }
 
 hipError_t launch_update_blocks(const StepParams& p, int param_bf16, int value_f32, int64_t first, int64_t count,
                                 hipStream_t stream) {
