@@ -148,8 +148,12 @@ template <bool GB, bool VF, int EF8>
 hipError_t launch_select_partials_t(const StepParams& p, hipStream_t stream) {
   if (p.block > kSubBlock) return launch_select_large<GB, VF, EF8, true>(p, 0, p.total_blocks, stream);
   const size_t lds = select_lds_words() * 4;
-  hipLaunchKernelGGL((select_kernel<64, true, GB, VF, EF8, true>), dim3((uint32_t)p.total_blocks), dim3(kWave), lds,
-                     stream, p, (int64_t)0, p.total_blocks);
+  if (select_dense<64>(p.k_full))
+    hipLaunchKernelGGL((select_kernel<64, true, GB, VF, EF8, true, true>), dim3((uint32_t)p.total_blocks), dim3(kWave),
+                       lds, stream, p, (int64_t)0, p.total_blocks);
+  else
+    hipLaunchKernelGGL((select_kernel<64, true, GB, VF, EF8, true>), dim3((uint32_t)p.total_blocks), dim3(kWave), lds,
+                       stream, p, (int64_t)0, p.total_blocks);
   return hipGetLastError();
 }
 

@@ -8,10 +8,162 @@
 namespace microadam {
 namespace {
 
+// ---------------------------------------------- denser selections (DENSE)
+// More than about 64 entries per row leave the half-lane maxima too coarse a
+// bound (the vectors above it overflow their LDS, and k > 128 has none), so
+// the lower bound L comes from the maxima of all 8-element vectors (the
+// largest 13-bit prefix with at least k of them at or above it), and every
+// lane appends its elements >= L (the candidates, about 1.25 k of them at 5%)
+// to LDS itself, in element order.  The k-th largest key is then found among
+// the candidates as in the general search, over ceil(C/64) registers instead
+// of the block's 64.  Returns false where the bound is 0 or the candidates
+// overflow: the caller then searches all elements.  120 M bf16 parameters at
+// k = 205: 218 -> 115 us, the candidates' three instructions per element and
+// the finer bound's ballots on top of a k = 41 select.
+constexpr int kDenseCand = 512;  // candidates held in LDS
+constexpr int kDenseMaxK = 384;  // rows of up to 384 entries fit the row buffer
+constexpr int kDenseRowWords = 2 * kDenseMaxK + 64;
+static_assert(2 * kDenseCand + 2 * kWave + kDenseRowWords <= (int)select_lds_words(),
+              "candidates, a sink per lane and the row in the kernel's LDS");
+
+template <int EPL, bool VF32>
+__device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], const float (&vmax)[EPL / 8],
+                                                uint32_t* smem, uint32_t eb, int kq, uint32_t row_lo, uint32_t row_hi,
+                                                uint32_t span_lo, uint32_t span_hi, uint32_t edge_off,
+                                                uint32_t edge_old, Rsrc rrec, uint32_t& T, uint32_t& i_last,
+                                                bool& notie) {
+  constexpr int NV = EPL / 8;
+  constexpr uint32_t EB = VF32 ? 8u : 4u;
+  using E = Entry<VF32>;
+  // values and indices of the candidates, each followed by a sink per lane
+  uint32_t* const cval = smem;
+  uint32_t* const cidx = smem + kDenseCand + kWave;
+  uint32_t* const rowbuf = smem + 2 * (kDenseCand + kWave);  // [kDenseRowWords] the new row's lines
+  const int lane = thread_id();
+
+  uint32_t Lb = 0;
+#pragma unroll
+  for (int bit = 30; bit >= 18; --bit) {
+    const uint32_t c = Lb | (1u << bit);
+    const float cf = __uint_as_float(c);
+    uint32_t n = 0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) n += popc(ballot(vmax[v] >= cf));
+    if ((int)n >= kq) Lb = c;
+  }
+  if (Lb == 0) return false;
+  const float L = __uint_as_float(Lb);
+
+  uint32_t cnt = 0;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cnt += __builtin_fabsf(a[v][e]) >= L ? 1u : 0u;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  uint32_t pos = 0, C = 0;
+#pragma unroll
+  for (int b = 0; b < 7; ++b) {
+    const uint64_t m = ballot((cnt >> b) & 1u);
+    pos += lanes_below(m) << b;
+    C += popc(m) << b;
+  }
+  if (C > (uint32_t)kDenseCand || C < (uint32_t)kq) return false;
+  {
+    // elements below L go to the lane's sink: no branch per element
+    const float L2 = opaque_f(L);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bool c = __builtin_fabsf(a[v][e]) >= L2;
+        const uint32_t at = c ? pos : (uint32_t)(kDenseCand + lane);
+        cval[at] = __float_as_uint(a[v][e]);
+        cidx[at] = eb + 8 * v + e;
+        pos += c ? 1u : 0u;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  wave_sync();
+
+  auto resolve = [&](auto ns_tag) {
+    constexpr int NS = decltype(ns_tag)::value;
+    uint32_t ck[NS];  // 0 past the candidates (whose keys are >= L > 0)
+#pragma unroll
+    for (int r = 0; r < NS; ++r) {
+      const uint32_t j = lane + kWave * r;
+      ck[r] = j < C ? cval[j] & 0x7FFFFFFFu : 0u;
+    }
+    // stops early once exactly k candidates are >= the threshold so far;
+    // below L the candidate count is not the block's, hence c >= L
+    uint32_t t = 0;
+    bool exact = false;
+#pragma unroll
+    for (int bit = 30; bit >= 0; --bit) {
+      if (!exact) {
+        const uint32_t c = t | (1u << bit);
+        uint32_t n = 0;
+#pragma unroll
+        for (int r = 0; r < NS; ++r) n += popc(ballot(ck[r] >= c));
+        if (n >= (uint32_t)kq) {
+          t = c;
+          exact = n == (uint32_t)kq && c >= Lb;
+        }
+      }
+    }
+    T = t;
+    uint32_t ngt = 0, neq = 0;
+    if (!exact) {
+#pragma unroll
+      for (int r = 0; r < NS; ++r) {
+        ngt += popc(ballot(ck[r] > t));
+        neq += popc(ballot(ck[r] == t));
+      }
+    }
+    const uint32_t need = exact ? 0u : (uint32_t)kq - ngt;  // keys equal to t that are kept, in element order
+    notie = exact || neq == need;
+    uint32_t eq_before = 0, sel_before = 0;
+#pragma unroll
+    for (int r = 0; r < NS; ++r) {
+      const uint32_t xv = cval[lane + kWave * r], xi = cidx[lane + kWave * r];  // past C: not selected
+      const bool gt = exact ? ck[r] >= t : ck[r] > t;
+      const bool eq = !exact && ck[r] == t;
+      const uint64_t em = ballot(eq);
+      const uint32_t rank = eq_before + lanes_below(em);
+      eq_before += popc(em);
+      const uint64_t lm = ballot(eq && rank == need - 1);
+      if (lm) i_last = __builtin_amdgcn_readlane(xi, (int)__builtin_ctzll(lm));
+      const bool sel = gt || (eq && rank < need);
+      const uint64_t sm = ballot(sel);
+      if (sel) {
+        const uint32_t w = ((row_lo - span_lo) >> 2) + (sel_before + lanes_below(sm)) * (EB / 4);
+        const typename E::T y = E::make(xi, __uint_as_float(xv));
+        if constexpr (VF32) *(u32x2*)(rowbuf + w) = y;
+        else rowbuf[w] = y;
+      }
+      sel_before += popc(sm);
+    }
+  };
+  const uint32_t ns = (C + kWave - 1) / kWave;
+  if (ns <= 2) resolve(std::integral_constant<int, 2>{});
+  else if (ns <= 4) resolve(std::integral_constant<int, 4>{});
+  else if (ns <= 6) resolve(std::integral_constant<int, 6>{});
+  else resolve(std::integral_constant<int, 8>{});
+  // the lines of the new row: the row, and the rest of the first and last
+  // line as read
+  if (edge_off < row_lo || edge_off >= row_hi) rowbuf[(edge_off - span_lo) >> 2] = edge_old;
+  wave_sync();
+  const uint32_t nvec4 = (span_hi - span_lo) >> 4;
+  for (uint32_t q = (uint32_t)lane; q < nvec4; q += kWave)
+    __builtin_amdgcn_raw_buffer_store_b128(*(const u32x4*)(rowbuf + 4 * q), rrec, span_lo + 16 * q, 0, kStream);
+  return true;
+}
+
 // Five waves per SIMD (96 registers; the kernel's 7.9 KB of LDS lets 20
 // waves share a compute unit): measured 3% faster than four on the
 // Llama-2-7B list (4.07 -> 3.95 ms), the few registers spilled included.
-template <int EPL, bool LB, bool GBF16, bool VF32, int EFM, bool LQ = false>
+template <int EPL, bool LB, bool GBF16, bool VF32, int EFM, bool LQ = false, bool DENSE = false>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5)))
 select_kernel(StepParams p, int64_t first, int64_t count) {
   static_assert(!LQ || (EPL == 64 && LB && (EFM & kEfRandom) == 0), "buckets spanning blocks: 64 per lane");
@@ -94,8 +246,12 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
 
   uint32_t T = 0, i_last = 0;
   bool notie = false;
-  bool general = kq > 2 * kWave;
-  if (!general) {
+  bool general = true;
+  if constexpr (DENSE) {
+    if (kq <= kDenseMaxK)
+      general = !dense_threshold<EPL, VF32>(a, vmax, smem, eb, kq, row_lo, row_hi, span_lo, span_hi, edge_off, edge_old,
+                                            rrec, T, i_last, notie);
+  } else if (kq <= 2 * kWave) {
     // stage 1: L over the half-lane maxima
     float h0 = vmax[0], h1 = vmax[NV / 2];
 #pragma unroll
@@ -123,8 +279,7 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
     }
     uint32_t nvec;
     const uint32_t pre = lane_prefix(cnt, nvec);
-    general = Lb == 0 || nvec > (uint32_t)kMaxCandVec;
-    if (!general) {
+    if (Lb != 0 && nvec <= (uint32_t)kMaxCandVec) {
       {
         uint32_t pos = pre;
 #pragma unroll
@@ -187,8 +342,8 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
       };
       if (nvec <= (uint32_t)kWave) gather(std::integral_constant<int, 1>{});
       else gather(std::integral_constant<int, 2>{});
-      general = C > (uint32_t)kCandMax || C < (uint32_t)kq;
-      if (!general) {
+      if (C <= (uint32_t)kCandMax && C >= (uint32_t)kq) {
+        general = false;
         wave_sync();
         // stage 3: the k-th largest key among the C candidates (NS slots of 64)
         auto resolve = [&](auto ns_tag) {
@@ -385,12 +540,26 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   }
 }
 
+// Whether rows of k entries take the DENSE form: from where the half-lane
+// maxima bound no longer pays (measured on 60 M parameters, select in us
+// without and with DENSE, B_d = 4096: k = 41 51 and 62, k = 58 56 and 57,
+// k = 70 69 and 54, k = 82 99 and 54, k = 205 125 and 60; B_d = 2048: k = 62
+// 58 and 60, k = 103 126 and 66).  Blocks of up to 1024 have no finer maxima.
+template <int EPL>
+bool select_dense(int k) {
+  return EPL == 64 ? k > 58 : EPL == 32 ? k > 64 : false;
+}
+
 template <int EPL, bool LB, bool GB, bool VF, int EFM>
 hipError_t launch_select_t(const StepParams& p, int64_t first, int64_t count, hipStream_t stream) {
   if (count <= 0) return hipSuccess;
   const size_t lds = select_lds_words() * 4;
-  hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM>), dim3((uint32_t)count), dim3(kWave), lds, stream, p,
-                     first, count);
+  if (select_dense<EPL>(p.k_full))
+    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM, false, (EPL > 16)>), dim3((uint32_t)count), dim3(kWave), lds,
+                       stream, p, first, count);
+  else
+    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM>), dim3((uint32_t)count), dim3(kWave), lds, stream, p, first,
+                       count);
   return hipGetLastError();
 }
 
