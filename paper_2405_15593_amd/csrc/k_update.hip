@@ -415,31 +415,41 @@ hipError_t launch_export(const StepParams& p, int64_t first_block, int64_t block
 
 }  // namespace
 
-size_t update_lds_max(int nt) { return nt == 64 ? update_lds_bytes<64, true>() : update_lds_bytes<256, true>(); }
+size_t update_lds_max(int nt) {
+  return nt == 64 ? update_lds_bytes<64, true>() : nt == 128 ? update_lds_bytes<128, true>() : update_lds_bytes<256, true>();
+}
+
+namespace {
+// The launch for a block size and types: f(threads, parameters are bf16,
+// window values are binary32), each as a compile-time constant.
+template <typename F>
+hipError_t by_form(int block, int param_bf16, int value_f32, F f) {
+  using Y = std::true_type;
+  using N = std::false_type;
+  auto types = [&](auto nt) {
+    if (param_bf16) return value_f32 ? f(nt, Y{}, Y{}) : f(nt, Y{}, N{});
+    return value_f32 ? f(nt, N{}, Y{}) : f(nt, N{}, N{});
+  };
+  switch (threads_for_block(block)) {
+    case 64: return types(std::integral_constant<int, 64>{});
+    case 128: return types(std::integral_constant<int, 128>{});
+    default: return types(std::integral_constant<int, 256>{});
+  }
+}
+}  // namespace
 
 hipError_t launch_update_blocks(const StepParams& p, int param_bf16, int value_f32, int64_t first, int64_t count,
                                 hipStream_t stream) {
-  if (threads_for_block(p.block) == 64) {
-    if (param_bf16)
-      return value_f32 ? launch_update_t<64, true, true>(p, first, count, stream)
-                       : launch_update_t<64, true, false>(p, first, count, stream);
-    return value_f32 ? launch_update_t<64, false, true>(p, first, count, stream)
-                     : launch_update_t<64, false, false>(p, first, count, stream);
-  }
-  if (param_bf16)
-    return value_f32 ? launch_update_t<256, true, true>(p, first, count, stream)
-                     : launch_update_t<256, true, false>(p, first, count, stream);
-  return value_f32 ? launch_update_t<256, false, true>(p, first, count, stream)
-                   : launch_update_t<256, false, false>(p, first, count, stream);
+  return by_form(p.block, param_bf16, value_f32, [&](auto nt, auto pb, auto vf) {
+    return launch_update_t<decltype(nt)::value, decltype(pb)::value, decltype(vf)::value>(p, first, count, stream);
+  });
 }
 
 hipError_t launch_moments_blocks(const StepParams& p, int64_t first_block, int64_t num_blocks, float* mhat,
                                  float* vhat, int value_f32, hipStream_t stream) {
-  if (threads_for_block(p.block) == 64)
-    return value_f32 ? launch_export<64, true>(p, first_block, num_blocks, mhat, vhat, stream)
-                     : launch_export<64, false>(p, first_block, num_blocks, mhat, vhat, stream);
-  return value_f32 ? launch_export<256, true>(p, first_block, num_blocks, mhat, vhat, stream)
-                   : launch_export<256, false>(p, first_block, num_blocks, mhat, vhat, stream);
+  return by_form(p.block, 0, value_f32, [&](auto nt, auto, auto vf) {
+    return launch_export<decltype(nt)::value, decltype(vf)::value>(p, first_block, num_blocks, mhat, vhat, stream);
+  });
 }
 
 }  // namespace microadam

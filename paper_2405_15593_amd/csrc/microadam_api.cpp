@@ -181,12 +181,10 @@ int make_plan(const microadam_config* c, const int64_t* numels, int32_t n, Tenso
   return MICROADAM_OK;
 }
 
-using microadam::threads_for_block;
-
 // Launch limits of a plan (blocks per launch; buckets spanning blocks).
 int check_launch_size(const microadam_config* cfg, const Planes& pl) {
   const int64_t total_blocks = pl.n_blocks;
-  const int nt = threads_for_block(cfg->topk_block);
+  const int nt = cfg->topk_block <= 1024 ? 64 : 256;  // threads per block of the widest launch
   if (total_blocks * (int64_t)nt >= ((int64_t)1 << 32) || total_blocks >= ((int64_t)1 << 31))
     return fail(MICROADAM_ERR_UNSUPPORTED, "too many Top-K blocks for one launch");
   if (pl.big && (total_blocks >= ((int64_t)1 << 28) || pl.table_bytes >= ((uint64_t)1 << 32)))

@@ -31,9 +31,9 @@ struct TensorDesc {
   int32_t reserved;
 };
 
-// Threads per workgroup for a Top-K block of B_d elements (each thread owns
-// 16 elements, so the block capacity is 16 * threads).
-inline int threads_for_block(int block) { return block <= 1024 ? 64 : 256; }
+// Threads per update workgroup for a Top-K block of up to 4096 elements (each
+// thread owns 16 elements, so the block capacity is 16 * threads).
+inline int threads_for_block(int block) { return block <= 1024 ? 64 : block <= 2048 ? 128 : 256; }
 
 // State layout: three planes indexed by the global block number gb.
 //   EF codes       ef_plane    + gb * B_d*b/8 (b = 4 or 8 bits per code)

@@ -28,6 +28,11 @@ CASES = {
     "block1024_k52_window20": dict(block=1024, density=0.05, window=20),  # 1040
     "block1024_largest_stage": dict(block=1024, density=0.074, window=20, param_dtype=bf16),  # 1520
     "block1024_above": dict(block=1024, density=0.075, window=20),        # 1540
+    # B_d = 2048, 128 threads
+    "block2048_window20": dict(block=2048, density=0.01, window=20, param_dtype=bf16),  # 420
+    "block1040_four_per_thread": dict(block=1040, bucket=16, density=0.05, window=9),  # 468
+    "block2048_largest_stage": dict(block=2048, density=0.0745, window=20),  # 3060
+    "block2048_above": dict(block=2048, density=0.075, window=20, param_dtype=bf16, grad_dtype=bf16, grad_scale=1e-3),
     # sqrt and division outside [2^-100, 2^100], eps outside it
     "small_moments": dict(window=3, grad_scale=1e-16, eps=1e-20),
     "large_moments": dict(window=3, grad_scale=1e18),
