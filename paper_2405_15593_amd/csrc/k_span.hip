@@ -150,7 +150,7 @@ hipError_t launch_select_partials_t(const StepParams& p, hipStream_t stream) {
   const size_t lds = select_lds_words() * 4;
   if (select_dense<64>(p.k_full))
     hipLaunchKernelGGL((select_kernel<64, true, GB, VF, EF8, true, true>), dim3((uint32_t)p.total_blocks), dim3(kWave),
-                       lds, stream, p, (int64_t)0, p.total_blocks);
+                       select_dense_lds<64>(), stream, p, (int64_t)0, p.total_blocks);
   else
     hipLaunchKernelGGL((select_kernel<64, true, GB, VF, EF8, true>), dim3((uint32_t)p.total_blocks), dim3(kWave), lds,
                        stream, p, (int64_t)0, p.total_blocks);

@@ -20,11 +20,15 @@ namespace {
 // overflow: the caller then searches all elements.  120 M bf16 parameters at
 // k = 205: 218 -> 115 us, the candidates' three instructions per element and
 // the finer bound's ballots on top of a k = 41 select.
-constexpr int kDenseCand = 512;  // candidates held in LDS
-constexpr int kDenseMaxK = 384;  // rows of up to 384 entries fit the row buffer
-constexpr int kDenseRowWords = 2 * kDenseMaxK + 64;
-static_assert(2 * kDenseCand + 2 * kWave + kDenseRowWords <= (int)select_lds_words(),
-              "candidates, a sink per lane and the row in the kernel's LDS");
+template <int EPL>
+struct Dense {
+  static constexpr int kCand = EPL == 64 ? 512 : EPL == 32 ? 384 : 256;  // candidates held in LDS
+  static constexpr int kMaxK = EPL == 64 ? 384 : EPL == 32 ? 256 : 128;  // entries of a row in the row buffer
+  static constexpr int kRowWords = 2 * kMaxK + 64;
+  // values and indices of the candidates, each followed by a sink per lane,
+  // and the new row's lines
+  static constexpr size_t kLdsWords = 2 * (kCand + kWave) + kRowWords;
+};
 
 template <int EPL, bool VF32>
 __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], const float (&vmax)[EPL / 8],
@@ -35,10 +39,10 @@ __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], co
   constexpr int NV = EPL / 8;
   constexpr uint32_t EB = VF32 ? 8u : 4u;
   using E = Entry<VF32>;
-  // values and indices of the candidates, each followed by a sink per lane
+  constexpr int kCand = Dense<EPL>::kCand;
   uint32_t* const cval = smem;
-  uint32_t* const cidx = smem + kDenseCand + kWave;
-  uint32_t* const rowbuf = smem + 2 * (kDenseCand + kWave);  // [kDenseRowWords] the new row's lines
+  uint32_t* const cidx = smem + kCand + kWave;
+  uint32_t* const rowbuf = smem + 2 * (kCand + kWave);  // the new row's lines
   const int lane = thread_id();
 
   uint32_t Lb = 0;
@@ -68,7 +72,7 @@ __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], co
     pos += lanes_below(m) << b;
     C += popc(m) << b;
   }
-  if (C > (uint32_t)kDenseCand || C < (uint32_t)kq) return false;
+  if (C > (uint32_t)kCand || C < (uint32_t)kq) return false;
   {
     // elements below L go to the lane's sink: no branch per element
     const float L2 = opaque_f(L);
@@ -77,7 +81,7 @@ __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], co
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const bool c = __builtin_fabsf(a[v][e]) >= L2;
-        const uint32_t at = c ? pos : (uint32_t)(kDenseCand + lane);
+        const uint32_t at = c ? pos : (uint32_t)(kCand + lane);
         cval[at] = __float_as_uint(a[v][e]);
         cidx[at] = eb + 8 * v + e;
         pos += c ? 1u : 0u;
@@ -146,10 +150,13 @@ __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], co
     }
   };
   const uint32_t ns = (C + kWave - 1) / kWave;
-  if (ns <= 2) resolve(std::integral_constant<int, 2>{});
+  if (EPL == 16 && ns <= 1) resolve(std::integral_constant<int, 1>{});
+  else if (ns <= 2) resolve(std::integral_constant<int, 2>{});
   else if (ns <= 4) resolve(std::integral_constant<int, 4>{});
-  else if (ns <= 6) resolve(std::integral_constant<int, 6>{});
-  else resolve(std::integral_constant<int, 8>{});
+  else if constexpr (kCand > 4 * kWave) {
+    if (ns <= 6) resolve(std::integral_constant<int, 6>{});
+    else if constexpr (kCand > 6 * kWave) resolve(std::integral_constant<int, 8>{});
+  }
   // the lines of the new row: the row, and the rest of the first and last
   // line as read
   if (edge_off < row_lo || edge_off >= row_hi) rowbuf[(edge_off - span_lo) >> 2] = edge_old;
@@ -160,12 +167,18 @@ __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], co
   return true;
 }
 
+template <int EPL, bool DENSE>
+constexpr int select_waves() {
+  return EPL == 16 ? 8 : EPL == 32 ? 6 : 5;
+}
+
 // Five waves per SIMD (96 registers; the kernel's 7.9 KB of LDS lets 20
 // waves share a compute unit): measured 3% faster than four on the
 // Llama-2-7B list (4.07 -> 3.95 ms), the few registers spilled included.
 template <int EPL, bool LB, bool GBF16, bool VF32, int EFM, bool LQ = false, bool DENSE = false>
-__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5)))
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(select_waves<EPL, DENSE>())))
 select_kernel(StepParams p, int64_t first, int64_t count) {
+  static_assert(DENSE || EPL == 64, "blocks of up to 2048 always take the DENSE form");
   static_assert(!LQ || (EPL == 64 && LB && (EFM & kEfRandom) == 0), "buckets spanning blocks: 64 per lane");
   constexpr int NV = EPL / 8;
   constexpr int CAP = kWave * EPL;
@@ -248,7 +261,7 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   bool notie = false;
   bool general = true;
   if constexpr (DENSE) {
-    if (kq <= kDenseMaxK)
+    if (kq <= Dense<EPL>::kMaxK)
       general = !dense_threshold<EPL, VF32>(a, vmax, smem, eb, kq, row_lo, row_hi, span_lo, span_hi, edge_off, edge_old,
                                             rrec, T, i_last, notie);
   } else if (kq <= 2 * kWave) {
@@ -540,26 +553,35 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   }
 }
 
-// Whether rows of k entries take the DENSE form: from where the half-lane
-// maxima bound no longer pays (measured on 60 M parameters, select in us
-// without and with DENSE, B_d = 4096: k = 41 51 and 62, k = 58 56 and 57,
-// k = 70 69 and 54, k = 82 99 and 54, k = 205 125 and 60; B_d = 2048: k = 62
-// 58 and 60, k = 103 126 and 66).  Blocks of up to 1024 have no finer maxima.
+// Whether rows of k entries take the DENSE form: with 64 elements per lane,
+// from where the half-lane maxima bound no longer pays (60 M parameters, B_d =
+// 4096, select in us without and with DENSE: k = 41 51 and 62, k = 58 56 and
+// 57, k = 70 69 and 54, k = 82 99 and 54, k = 205 125 and 60); blocks of up to
+// 2048 always, since its smaller LDS and registers let six to eight waves per
+// SIMD run where the other form had five (B_d = 1024: 80 -> 60 at k = 11; B_d =
+// 2048: 50 -> 48 at k = 21, 126 -> 52 at k = 103).
 template <int EPL>
 bool select_dense(int k) {
-  return EPL == 64 ? k > 58 : EPL == 32 ? k > 64 : false;
+  return EPL < 64 || k > 58;
+}
+
+// LDS bytes of the DENSE form (with 64 elements per lane the block's exchange
+// passes through the same LDS).
+template <int EPL>
+constexpr size_t select_dense_lds() {
+  const size_t w = Dense<EPL>::kLdsWords * 4;
+  return EPL == 64 && w < kTrBytes ? kTrBytes : w;
 }
 
 template <int EPL, bool LB, bool GB, bool VF, int EFM>
 hipError_t launch_select_t(const StepParams& p, int64_t first, int64_t count, hipStream_t stream) {
   if (count <= 0) return hipSuccess;
-  const size_t lds = select_lds_words() * 4;
   if (select_dense<EPL>(p.k_full))
-    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM, false, (EPL > 16)>), dim3((uint32_t)count), dim3(kWave), lds,
-                       stream, p, first, count);
-  else
-    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM>), dim3((uint32_t)count), dim3(kWave), lds, stream, p, first,
-                       count);
+    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM, false, true>), dim3((uint32_t)count), dim3(kWave),
+                       select_dense_lds<EPL>(), stream, p, first, count);
+  else if constexpr (EPL == 64)
+    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM>), dim3((uint32_t)count), dim3(kWave),
+                       select_lds_words() * 4, stream, p, first, count);
   return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
-"""The select's form for denser rows (blocks of 1025 to 4096 elements, k above
-58 or 64) where it can go wrong: the smallest and largest k of its range, tie
+"""The select's form for denser rows (k above 58 of 4096) and for every block of
+up to 2048 elements, where it can go wrong: the smallest and largest k of its range, tie
 groups across the threshold, a zero bound and overflowing candidates (both
 fall back to the search over all elements), ragged tails with few entries, and
 the error-feedback formats.  State bit for bit against the oracle."""
@@ -25,6 +25,13 @@ CASES = {
     "zero_bound": dict(density=0.05, grad_dist="sparse_spikes", degenerate=True),
     "block2048_k65": dict(block=2048, density=65 / 2048, **BF),
     "block2048_k103_ties": dict(block=2048, density=0.05, grad_dist="student_t2_snapped64", **BF),
+    "block2048_k256": dict(block=2048, density=0.125, window=2),
+    "block2048_k257": dict(block=2048, density=257 / 2048, window=2),
+    "block2048_f32_values": dict(block=2048, density=0.1, value_f32=True),
+    "block1024_k128": dict(block=1024, density=0.125, window=2, **BF),
+    "block1024_k129": dict(block=1024, density=129 / 1024, window=2, **BF),
+    "block1024_ties": dict(block=1024, density=0.05, grad_dist="student_t2_snapped64", value_f32=True),
+    "block512_signs": dict(block=512, density=0.02, grad_dist="signs", degenerate=True),
     "block3008_bucket16": dict(block=3008, bucket=16, density=0.04),
     "ef8": dict(density=0.03, ef_bits=8, **BF),
     "randomized": dict(density=0.03, ef_rounding=1, ef_seed=11, **BF),
