@@ -6,11 +6,15 @@
 namespace microadam {
 namespace {
 
-// One thread per bucket of the step (all tensors): the (min, max) over the
-// partials of the blocks it covers, -0 stored as +0, into table t mod 2.
-__global__ void __launch_bounds__(256) bucket_reduce_kernel(StepParams p) {
-  const int64_t cg = (int64_t)block_id() * 256 + thread_id();
-  if (cg >= p.total_buckets) return;
+// Per bucket of the step (all tensors), by a group of 2^lg lanes: the (min,
+// max) over the partials of the blocks it covers, -0 stored as +0, into table
+// t mod 2.  The host takes the group from the blocks per bucket: with one
+// thread per bucket of 100,000 elements, the 26 loads of a bucket followed
+// each other in 16 workgroups (17 us per 405 M parameters; 4 us with 32 lanes).
+__global__ void __launch_bounds__(256) bucket_reduce_kernel(StepParams p, int32_t lg) {
+  const int64_t cg = ((int64_t)block_id() * 256 + thread_id()) >> lg;
+  const int i0 = thread_id() & ((1 << lg) - 1);
+  if (cg >= p.total_buckets) return;  // whole groups
   const __attribute__((address_space(4))) TensorDesc* td = constant_ptr(p.tensors);
   int lo = 0, hi = p.n_tensors - 1;  // the last tensor whose buckets start at or before cg
   while (lo < hi) {
@@ -24,15 +28,22 @@ __global__ void __launch_bounds__(256) bucket_reduce_kernel(StepParams p) {
   const int64_t e_lo = c * bq;
   const int64_t e_hi = e_lo + bq < d.numel ? e_lo + bq : d.numel;
   const int64_t q_lo = e_lo / B, q_hi = (e_hi - 1) / B;
+  // only the bucket's first block can hold another bucket's end before it
+  const bool straddles = q_lo * B < e_lo;
   const Rsrc rp = make_rsrc(p.state + p.partial_plane, (uint32_t)(p.total_blocks * 16));
   float mn = __builtin_inff(), mx = -__builtin_inff();
-  for (int64_t q = q_lo; q <= q_hi; ++q) {
+  for (int64_t q = q_lo + i0; q <= q_hi; q += (int64_t)1 << lg) {
     const int64_t gb = q == d.num_blocks - 1 ? d.last_block : d.first_block + q;
-    const uint32_t part = (q * B) / bq == c ? 0u : 8u;  // the block's first bucket, or its second
+    const uint32_t part = q == q_lo && straddles ? 8u : 0u;  // the block's second bucket, or its first
     const u32x2 pr = __builtin_amdgcn_raw_buffer_load_b64(rp, (uint32_t)(gb * 16) + part, 0, 0);
     mn = __builtin_fminf(mn, __uint_as_float(pr[0]));
     mx = __builtin_fmaxf(mx, __uint_as_float(pr[1]));
   }
+  for (int x = (1 << lg) >> 1; x > 0; x >>= 1) {
+    mn = __builtin_fminf(mn, __shfl_xor(mn, x, kWave));
+    mx = __builtin_fmaxf(mx, __shfl_xor(mx, x, kWave));
+  }
+  if (i0 != 0) return;
   mn = mn + 0.0f;  // a bucket bound of -0 is stored as +0
   mx = mx + 0.0f;
   const uint64_t t = (uint64_t)(p.t & 1);
@@ -49,32 +60,53 @@ __global__ void __launch_bounds__(256) bucket_reduce_kernel(StepParams p) {
 // 64 elements per lane.  Above 4096 the sub-block's entries of the new row
 // are those of its four 1024-element quarters, found through the record's
 // segment table.
+//
+// Blocks that are whole sub-blocks come and go as contiguous kilobytes through
+// LDS (coalesced_exchange).  A lane decodes and quantizes with the pairs of its
+// first element's bucket (codes from two bracketing products instead of an IEEE
+// division, as in the select); elements past a bucket's end inside a lane's run
+// are then done again with the next one's (a uniform branch, one block in 24
+// with buckets of 100,000).
+// Two Llama-2-7B layers (405 M bf16 parameters): @RQ@.
 template <bool GBF16, bool VF32, int EFM>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 requant_kernel(StepParams p, int64_t first, int64_t count, int32_t nsub) {
   constexpr int EPL = 64, NV = EPL / 8, CAP = kWave * EPL;
   constexpr int CW = (EFM & kEf8) ? 2 : 1;
+  constexpr uint32_t kTr = GBF16 ? kTrBytes : kTrBytesF32;
   using E = Entry<VF32>;
+  __shared__ __align__(16) uint32_t tr[kTr / 4];
   __shared__ uint32_t kept[CAP / 32];  // bit i: element off + i is in the new row
 
   const int lane = thread_id();
   const int64_t w = xcd_block(block_id(), count * nsub);
   const int64_t gb = first + w / nsub;
   const uint32_t off = (uint32_t)(w % nsub) * CAP;  // the sub-block's first element
-  const uint32_t eb = off + (uint32_t)lane * EPL;   // the lane's first element in the block
+  const uint32_t el = (uint32_t)lane * EPL;         // the lane's first element in the sub-block
+  const uint32_t eb = off + el;                     // and in the block
+  const uint32_t sub_ef = (EFM & kEf8) ? (uint32_t)CAP : (uint32_t)CAP / 2;
   const uint32_t ef_bytes = (EFM & kEf8) ? (uint32_t)p.block : (uint32_t)(p.block >> 1);
-  const Rsrc re = make_rsrc(p.state + p.ef_plane + (uint64_t)gb * ef_bytes, ef_bytes);
-  // 16-byte code accesses when no lane's codes straddle the end of the block's
-  const bool wide = p.block % CAP == 0;
+  const bool coal = p.block % CAP == 0;
+  const uint32_t ef_off = (EFM & kEf8) ? off : off / 2;
+  const uint32_t ef_here = ef_bytes - ef_off < sub_ef ? ef_bytes - ef_off : sub_ef;
+  const Rsrc re = make_rsrc(p.state + p.ef_plane + (uint64_t)gb * ef_bytes + ef_off, ef_here);
   LaneIn<EPL, true, GBF16, EFM> in;
-  lane_load_codes(in, re, eb, wide);
   const Block b = locate(p, gb);
-  const int s = b.s, kq = b.kq;
-  if ((int)off >= s) return;  // a sub-block past the end of a ragged block
-  const bool full = s - (int)off >= CAP;
-  const Rsrc rg = make_rsrc((const uint8_t*)b.desc.grad + b.e0 * (GBF16 ? 2 : 4), vec_bytes<GBF16>(s));
-  lane_load_grad(in, rg, eb);
+  const int s = b.s - (int)off, kq = b.kq;
+  if (s <= 0) return;  // a sub-block past the end of a ragged block
+  const bool full = s >= CAP;
+  const Rsrc rg = make_rsrc((const uint8_t*)b.desc.grad + (b.e0 + off) * (GBF16 ? 2 : 4),
+                            vec_bytes<GBF16>(full ? CAP : s));
   const LqBuckets old_b = lq_buckets(p, b, eb, EPL, 0), new_b = lq_buckets(p, b, eb, EPL, 1);
+  if (coal) {
+    CoalescedIn<GBF16> cx;
+    coalesced_load_codes<EFM>(cx, re, lane);
+    coalesced_load_grad(cx, rg, lane);
+    coalesced_exchange(cx, in, tr, lane);
+  } else {
+    lane_load_codes(in, re, el, false);
+    lane_load_grad(in, rg, el);
+  }
 
   kept[lane] = 0u;
   kept[lane + kWave] = 0u;
@@ -102,58 +134,76 @@ requant_kernel(StepParams p, int64_t first, int64_t count, int32_t nsub) {
   wave_sync();
 
   float a[NV][8];
-  const int rem = s - (int)eb;
-  lane_decode_lq(in, old_b, a, rem, full);
+  const int rem = s - (int)el;
   const uint32_t k0 = kept[2 * lane], k1 = kept[2 * lane + 1];  // this lane's 64 elements
-#pragma unroll
-  for (int v = 0; v < NV; ++v)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int i = 8 * v + e;
-      const uint32_t bit = i < 32 ? (k0 >> i) & 1u : (k1 >> (i - 32)) & 1u;
-      if (bit) a[v][e] = 0.0f;
-    }
-
-  const float lo0 = __uint_as_float(new_b.st[0][0]), u0 = ef_step<EFM>(__uint_as_float(new_b.st[0][1]) - lo0);
-  const float lo1 = __uint_as_float(new_b.st[1][0]), u1 = ef_step<EFM>(__uint_as_float(new_b.st[1][1]) - lo1);
   const EfStream st{b.e0, b.j, (uint32_t)p.t, p.seed_lo, p.seed_hi};
-  constexpr float L = (EFM & kEf8) ? 255.0f : 15.0f;
   uint32_t wv[NV * CW];
+  auto zero_kept = [&] {
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int i = 8 * v + e;
+        // all ones where the bit is set
+        const int32_t m = (int32_t)((i < 32 ? k0 : k1) << (31 - (i & 31))) >> 31;
+        a[v][e] = __uint_as_float(__float_as_uint(a[v][e]) & ~(uint32_t)m);
+      }
+  };
+  in.st[0] = old_b.st[0];
+  lane_decode(in, a, rem, full);
+  lane_decode_second<EPL, GBF16, EFM>(a, old_b, re, rg, el, rem);
+  zero_kept();
+  const float lo = __uint_as_float(new_b.st[0][0]), u = ef_step<EFM>(__uint_as_float(new_b.st[0][1]) - lo);
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    // each element against its own bucket's pair, with an IEEE division
-    uint32_t w24[8] = {};
-    if constexpr ((EFM & kEfRandom) != 0) philox_w24((uint64_t)(b.e0 + eb + 8 * v) >> 2, st, w24);
-    uint32_t w[CW];
+    uint32_t c[CW];
+    vector_codes<EFM>(a[v], lo, u, (uint64_t)(b.e0 + eb + 8 * v) >> 2, st, c);
 #pragma unroll
-    for (int c = 0; c < CW; ++c) w[c] = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const bool second = 8 * v + e >= new_b.sp;
-      const float lo = second ? lo1 : lo0, u = second ? u1 : u0;
-      uint32_t code = 0;
-      if (u != 0.0f)
-        code = (EFM & kEfRandom) ? code_randomized(a[v][e], lo, u, L, w24[e]) : code_nearest(a[v][e], lo, u, L);
-      if (8 * v + e >= rem) code = 0;  // past the block's end
-      if constexpr (EFM & kEf8) w[e >> 2] |= code << (8 * (e & 3));
-      else w[0] |= code << (4 * e);
-    }
-#pragma unroll
-    for (int c = 0; c < CW; ++c) wv[CW * v + c] = w[c];
+    for (int h = 0; h < CW; ++h) wv[CW * v + h] = c[h];
   }
-  if ((int)eb < s) lane_store_codes<EPL, EFM>(wv, eb, wide, re);
+  if (ballot(new_b.sp < EPL) != 0) {  // the elements in the lane's second bucket
+    const float lo1 = __uint_as_float(new_b.st[1][0]), u1 = ef_step<EFM>(__uint_as_float(new_b.st[1][1]) - lo1);
+    const int sp = opaque_v(new_b.sp), eo = opaque_v((int)eb);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      __builtin_amdgcn_sched_barrier(0);
+      uint32_t c[CW];
+      vector_codes<EFM>(a[v], lo1, u1, (uint64_t)(b.e0 + eo + 8 * v) >> 2, st, c);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t m = (EFM & kEf8) ? 0xFFu << (8 * (e & 3)) : 0xFu << (4 * e);
+        uint32_t& w0 = wv[(EFM & kEf8) ? CW * v + (e >> 2) : v];
+        if (8 * v + e >= sp) w0 = (w0 & ~m) | (c[(EFM & kEf8) ? e >> 2 : 0] & m);
+      }
+    }
+  }
+  if (!full) {  // codes past the block's end are 0
+    const int r = opaque_v(rem);
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (8 * v + e >= r) {
+          if constexpr (EFM & kEf8) wv[CW * v + (e >> 2)] &= ~(0xFFu << (8 * (e & 3)));
+          else wv[v] &= ~(0xFu << (4 * e));
+        }
+  }
+  if (coal) lane_store_codes_coalesced<EFM>(wv, tr, re);
+  else if ((int)el < s) lane_store_codes<EPL, EFM>(wv, el, false, re);
 }
 
 template <bool GB, bool VF, int EF8>
 hipError_t launch_select_partials_t(const StepParams& p, hipStream_t stream) {
   if (p.block > kSubBlock) return launch_select_large<GB, VF, EF8, true>(p, 0, p.total_blocks, stream);
-  const size_t lds = select_lds_words() * 4;
-  if (select_dense<64>(p.k_full))
-    hipLaunchKernelGGL((select_kernel<64, true, GB, VF, EF8, true, true>), dim3((uint32_t)p.total_blocks), dim3(kWave),
-                       select_dense_lds<64>(), stream, p, (int64_t)0, p.total_blocks);
-  else
+  if (select_dense<64, VF>(p.k_full)) {
+    const size_t lds = select_lds<64, GB, !VF>();
+    hipLaunchKernelGGL((select_kernel<64, true, GB, VF, EF8, true, !VF>), dim3((uint32_t)p.total_blocks), dim3(kWave),
+                       lds, stream, p, (int64_t)0, p.total_blocks);
+  } else {
+    const size_t lds = select_lds<64, GB, false>();
     hipLaunchKernelGGL((select_kernel<64, true, GB, VF, EF8, true>), dim3((uint32_t)p.total_blocks), dim3(kWave), lds,
                        stream, p, (int64_t)0, p.total_blocks);
+  }
   return hipGetLastError();
 }
 
@@ -193,8 +243,11 @@ hipError_t launch_select_partials(const StepParams& p, int grad_bf16, int value_
 
 hipError_t launch_bucket_reduce(const StepParams& p, hipStream_t stream) {
   if (p.total_buckets <= 0) return hipSuccess;
-  const uint32_t grid = (uint32_t)((p.total_buckets + 255) / 256);
-  hipLaunchKernelGGL(bucket_reduce_kernel, dim3(grid), dim3(256), 0, stream, p);
+  // lanes per bucket: the blocks a bucket covers, up to a wave
+  int32_t lg = 0;
+  while (lg < 6 && (int64_t)p.block << lg < p.big_bucket + p.block) ++lg;
+  const uint32_t grid = (uint32_t)(((p.total_buckets << lg) + 255) / 256);
+  hipLaunchKernelGGL(bucket_reduce_kernel, dim3(grid), dim3(256), 0, stream, p, lg);
   return hipGetLastError();
 }
 

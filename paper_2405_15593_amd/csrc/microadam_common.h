@@ -729,6 +729,44 @@ __device__ __forceinline__ void lane_decode_lq(const LaneIn<EPL, true, GBF16, EF
   }
 }
 
+// The lanes' elements in their second bucket, after a decode of all with the
+// first one's pair: only where some lane's run straddles two buckets (a
+// uniform branch, one block in 24 with buckets of 100,000), with the inputs
+// loaded again, vector by vector, so that they need not stay in registers.
+// re, rg: codes and gradient, the lane's run starting at element eb of both.
+template <int EPL, bool GBF16, int EFM>
+__device__ __forceinline__ void lane_decode_second(float (&a)[EPL / 8][8], const LqBuckets& bk, Rsrc re, Rsrc rg,
+                                                   uint32_t eb, int rem) {
+  if (ballot(bk.sp < EPL) == 0) return;
+  const float lo = __uint_as_float(bk.st[1][0]), u = ef_step<EFM>(__uint_as_float(bk.st[1][1]) - lo);
+  const int sp = opaque_v(bk.sp), r = opaque_v(rem);
+  eb = (uint32_t)opaque_v((int)eb);  // (not merged with the first loads)
+#pragma unroll
+  for (int v = 0; v < EPL / 8; ++v) {
+    __builtin_amdgcn_sched_barrier(0);  // one vector's inputs at a time
+    const Raw8<GBF16> raw = load8<GBF16>(rg, eb + 8 * v);
+    uint32_t cw[2] = {};
+    if constexpr (EFM & kEf8) {
+      const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(re, eb + 8 * v, 0, 0);
+      cw[0] = t[0];
+      cw[1] = t[1];
+    } else {
+      cw[0] = __builtin_amdgcn_raw_buffer_load_b32(re, (eb >> 1) + 4 * v, 0, 0);
+    }
+    float g[8], c[8];
+    unpack8<GBF16>(raw, g);
+    unpack_codes<EFM>(cw, 0, c);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float sc = c[e] * u;
+      const float d = sc + lo;
+      const float x = g[e] + d;
+      if ((8 * v + e >= sp) & (8 * v + e < r)) a[v][e] = x;
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 template <int EPL>
 __device__ __forceinline__ void lane_vmax(const float (&a)[EPL / 8][8], float (&vmax)[EPL / 8]) {
 #pragma unroll
@@ -869,7 +907,7 @@ __device__ __forceinline__ void lane_store_codes(const uint32_t (&wv)[(EPL / 8) 
 
 // ------------------------------------- coalesced block loads and stores
 // One wave over a 4096-element block (64 elements per lane: lane l owns
-// [64l, 64l + 64)) with bf16 gradients.  A lane's own run is 128 bytes of
+// [64l, 64l + 64)).  A lane's own run is 128 (bf16) or 256 (binary32) bytes of
 // gradient and 32 (4-bit) or 64 (8-bit) bytes of codes, so loading it
 // directly gives every 16-byte access of the wave a 128-byte (or 32- or
 // 64-byte) stride.  Instead
@@ -882,34 +920,40 @@ __device__ __forceinline__ void lane_store_codes(const uint32_t (&wv)[(EPL / 8) 
 //   4-bit codes: code byte c at kTrCodes + c + 16*(c / 32), 3072 bytes;
 //   8-bit codes: code byte c at c + 16*(c / 64), 5120 bytes, exchanged
 //     before the gradient through the start of the same LDS.
+//   binary32 gradient: element e of a half block (accesses 0-7 or 8-15) at
+//     4e + 16*(e / 64), 8704 bytes per half, after the codes (a half at a time
+//     keeps the loaded and the handed-over vectors below 100 registers).
 // The two halves of the gradient pass one after the other through the same
-// 4608 bytes, so the exchange needs 7680 bytes of LDS.
+// bytes, so the exchange needs 7680 (bf16) or 8704 (binary32) bytes of LDS.
 constexpr uint32_t kTrCodes = 4608;
 constexpr uint32_t kTrBytes = 7680;
+constexpr uint32_t kTrBytesF32 = 8704;
 constexpr uint32_t kTrCodes8Bytes = 5120;
 static_assert(kTrBytes <= select_lds_words() * 4, "the exchange reuses the select kernel's LDS");
 static_assert(kTrCodes8Bytes <= kTrBytes, "the 8-bit code exchange fits the same LDS");
 
+template <bool GBF16>
 struct CoalescedIn {
-  u32x4 g[8];
+  u32x4 g[GBF16 ? 8 : 16];
   u32x4 c[4];  // codes: 2 accesses (4-bit) or 4 (8-bit)
 };
 
-template <int EFM>
-__device__ __forceinline__ void coalesced_load_codes(CoalescedIn& x, Rsrc re, int lane) {
+template <int EFM, bool GBF16>
+__device__ __forceinline__ void coalesced_load_codes(CoalescedIn<GBF16>& x, Rsrc re, int lane) {
 #pragma unroll
   for (int q = 0; q < ((EFM & kEf8) ? 4 : 2); ++q)
     x.c[q] = __builtin_amdgcn_raw_buffer_load_b128(re, 1024 * q + 16 * lane, 0, kStream);
 }
-__device__ __forceinline__ void coalesced_load_grad(CoalescedIn& x, Rsrc rg, int lane) {
+template <bool GBF16>
+__device__ __forceinline__ void coalesced_load_grad(CoalescedIn<GBF16>& x, Rsrc rg, int lane) {
 #pragma unroll
-  for (int v = 0; v < 8; ++v) x.g[v] = __builtin_amdgcn_raw_buffer_load_b128(rg, 1024 * v + 16 * lane, 0, kStream);
+  for (int v = 0; v < (GBF16 ? 8 : 16); ++v) x.g[v] = __builtin_amdgcn_raw_buffer_load_b128(rg, 1024 * v + 16 * lane, 0, kStream);
 }
 
 // Hands the loaded block to the lanes that own it: lane l's gradient vectors
 // (8 elements each) and code words (8 codes each) in element order.
-template <bool LB, int EFM>
-__device__ __forceinline__ void coalesced_exchange(const CoalescedIn& x, LaneIn<64, LB, true, EFM>& in,
+template <bool LB, bool GBF16, int EFM>
+__device__ __forceinline__ void coalesced_exchange(const CoalescedIn<GBF16>& x, LaneIn<64, LB, GBF16, EFM>& in,
                                                    uint32_t* lds, int lane) {
   constexpr bool EF8 = (EFM & kEf8) != 0;
   uint8_t* const b = (uint8_t*)lds;
@@ -928,26 +972,52 @@ __device__ __forceinline__ void coalesced_exchange(const CoalescedIn& x, LaneIn<
     }
     wave_sync();
   }
+  auto codes_in = [&] {
+    if constexpr (!EF8) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        *(u32x4*)(b + kTrCodes + 1536 * q + 16 * lane + 16 * (lane >> 1)) = x.c[q];
+    }
+  };
+  auto codes_out = [&] {
+    if constexpr (!EF8) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const u32x4 t = *(const u32x4*)(b + kTrCodes + 48 * lane + 16 * h);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) in.cw[4 * h + j] = t[j];
+      }
+    }
+  };
+  if constexpr (!GBF16) {
+    codes_in();
+    wave_sync();
+    codes_out();
+    wave_sync();
+    const uint32_t wr = 272u * (uint32_t)(lane >> 4) + 16u * (uint32_t)(lane & 15);  // + 1088v: access v of the half
+    const uint32_t rd = 272u * (uint32_t)(lane & 31);                                // + 16j: this lane's chunk j
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int v = 0; v < 8; ++v) *(u32x4*)(b + 1088 * v + wr) = x.g[8 * h + v];
+      wave_sync();
+      if ((lane >> 5) == h) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) in.graw[j >> 1].w[j & 1] = *(const u32x4*)(b + rd + 16 * j);
+      }
+      wave_sync();
+    }
+    return;
+  } else {
 #pragma unroll
   for (int v = 0; v < 4; ++v) *(u32x4*)(b + 1152 * v + wg) = x.g[v];
-  if constexpr (!EF8) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-      *(u32x4*)(b + kTrCodes + 1536 * q + 16 * lane + 16 * (lane >> 1)) = x.c[q];
-  }
+  codes_in();
   wave_sync();
   if (lane < 32) {
 #pragma unroll
     for (int v = 0; v < 8; ++v) in.graw[v].w[0] = *(const u32x4*)(b + rg + 16 * v);
   }
-  if constexpr (!EF8) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const u32x4 t = *(const u32x4*)(b + kTrCodes + 48 * lane + 16 * h);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) in.cw[4 * h + j] = t[j];
-    }
-  }
+  codes_out();
   wave_sync();
 #pragma unroll
   for (int v = 0; v < 4; ++v) *(u32x4*)(b + 1152 * v + wg) = x.g[4 + v];
@@ -957,6 +1027,7 @@ __device__ __forceinline__ void coalesced_exchange(const CoalescedIn& x, LaneIn<
     for (int v = 0; v < 8; ++v) in.graw[v].w[0] = *(const u32x4*)(b + rg + 16 * v);
   }
   wave_sync();
+  }
 }
 
 // Stores the lane's codes (4-bit: one word per vector; 8-bit: two) through
@@ -1170,22 +1241,32 @@ __device__ __forceinline__ void wave_partials(const float (&a)[EPL / 8][8], cons
   const int lsplit = ls < 0 ? 0 : ls > EPL ? EPL : (int)ls;
   const int r = opaque_v(rem);
   float mn0 = __builtin_inff(), mx0 = -__builtin_inff(), mn1 = __builtin_inff(), mx1 = -__builtin_inff();
+  if (ballot(rem < EPL || lsplit < EPL) == 0) {  // every lane's run whole and in the first bucket
 #pragma unroll
-  for (int v = 0; v < NV; ++v)
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int i = 8 * v + e;
-      const float x = a[v][e];
-      if (i < r) {
-        if (i < lsplit) {
-          mn0 = __builtin_fminf(mn0, x);
-          mx0 = __builtin_fmaxf(mx0, x);
-        } else {
-          mn1 = __builtin_fminf(mn1, x);
-          mx1 = __builtin_fmaxf(mx1, x);
+      for (int e = 0; e < 8; ++e) {
+        mn0 = __builtin_fminf(mn0, a[v][e]);
+        mx0 = __builtin_fmaxf(mx0, a[v][e]);
+      }
+  } else {
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int i = 8 * v + e;
+        const float x = a[v][e];
+        if (i < r) {
+          if (i < lsplit) {
+            mn0 = __builtin_fminf(mn0, x);
+            mx0 = __builtin_fmaxf(mx0, x);
+          } else {
+            mn1 = __builtin_fminf(mn1, x);
+            mx1 = __builtin_fmaxf(mx1, x);
+          }
         }
       }
-    }
+  }
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
     mn0 = __builtin_fminf(mn0, __shfl_xor(mn0, d, kWave));

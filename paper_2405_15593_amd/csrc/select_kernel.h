@@ -167,16 +167,24 @@ __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], co
   return true;
 }
 
-template <int EPL, bool DENSE>
-constexpr int select_waves() {
-  return EPL == 16 ? 8 : EPL == 32 ? 6 : 5;
+template <int EPL, bool GBF16, int EFM>
+constexpr bool select_coalesced() {
+  return EPL == 64 && (!GBF16 || (EFM & kEf8) == 0);
+}
+template <int EPL>
+constexpr int select_waves(bool grad_bf16) {
+  return EPL == 16 ? 8 : EPL == 32 ? 6 : grad_bf16 ? 5 : 4;
 }
 
 // Five waves per SIMD (96 registers; the kernel's 7.9 KB of LDS lets 20
 // waves share a compute unit): measured 3% faster than four on the
 // Llama-2-7B list (4.07 -> 3.95 ms), the few registers spilled included.
+// Binary32 gradients take four: the loaded half of a block and the lane's 64
+// elements need 125 registers (per 1e9 parameters 1353 us with each lane
+// loading its own 256-byte run, five waves; 944 us coalesced through LDS,
+// 5.7 TB/s).
 template <int EPL, bool LB, bool GBF16, bool VF32, int EFM, bool LQ = false, bool DENSE = false>
-__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(select_waves<EPL, DENSE>())))
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(select_waves<EPL>(GBF16))))
 select_kernel(StepParams p, int64_t first, int64_t count) {
   static_assert(DENSE || EPL == 64, "blocks of up to 2048 always take the DENSE form");
   static_assert(!LQ || (EPL == 64 && LB && (EFM & kEfRandom) == 0), "buckets spanning blocks: 64 per lane");
@@ -202,22 +210,23 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   const Rsrc re = make_rsrc(p.state + p.ef_plane + (uint64_t)gb * ef_bytes, ef_bytes);
   const Rsrc rs = make_rsrc(p.state + p.stats_plane + (uint64_t)gb * nbk * 8, nbk * 8);
   const bool wide = p.block == CAP;
-  // 4096-element blocks of bf16 gradients with 4-bit codes load and store
-  // the block as contiguous kilobytes and exchange it through LDS
-  // (coalesced_exchange); the other shapes load each lane's run directly
-  // (with 8-bit codes the exchange measured slower here: 5.95 vs 5.75 ms on
-  // the Llama-2-7B list)
-  constexpr bool kCoal = EPL == 64 && GBF16 && (EFM & kEf8) == 0 && !LQ;
+  // 4096-element blocks load and store the block as contiguous kilobytes and
+  // exchange it through LDS (coalesced_exchange); the other shapes load each
+  // lane's run directly, and so do bf16 gradients with 8-bit codes (there the
+  // exchange measured slower: 5.95 vs 5.75 ms on the Llama-2-7B list)
+  constexpr bool kCoal = select_coalesced<EPL, GBF16, EFM>();
   const bool coal = kCoal && wide;
   LaneIn<EPL, LB, GBF16, EFM> in;
-  CoalescedIn cx;
-  if constexpr (LQ) {
-    lane_load_codes(in, re, eb, wide);
-  } else if (coal) {
+  CoalescedIn<GBF16> cx;
+  if (coal) {
+    if constexpr (!LQ) {
 #pragma unroll
-    for (int v = 0; v < (LB ? 1 : EPL / 8); ++v)
-      in.st[v] = __builtin_amdgcn_raw_buffer_load_b64(rs, ((eb + 8 * v) >> bl) * 8, 0, kStream);
+      for (int v = 0; v < (LB ? 1 : EPL / 8); ++v)
+        in.st[v] = __builtin_amdgcn_raw_buffer_load_b64(rs, ((eb + 8 * v) >> bl) * 8, 0, kStream);
+    }
     coalesced_load_codes<EFM>(cx, re, lane);
+  } else if constexpr (LQ) {
+    lane_load_codes(in, re, eb, wide);
   } else {
     lane_load_state(in, re, rs, eb, bl, wide);
   }
@@ -227,8 +236,10 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   const int s = b.s, kq = b.kq;
   const bool full = s == CAP;
   const Rsrc rg = make_rsrc((const uint8_t*)b.desc.grad + b.e0 * (GBF16 ? 2 : 4), vec_bytes<GBF16>(s));
-  if (coal) coalesced_load_grad(cx, rg, lane);
-  else lane_load_grad(in, rg, eb);
+  if constexpr (GBF16) {
+    if (coal) coalesced_load_grad(cx, rg, lane);
+    else lane_load_grad(in, rg, eb);
+  }
   // The new row, bytes [row_lo, row_hi) of the block's window record, is
   // written as the whole 128-byte lines [span_lo, span_hi) that cover it
   // (records are whole lines): partial-line writes cost the memory system
@@ -241,15 +252,35 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   const Rsrc rrec = make_rsrc(p.state + p.win_plane + (uint64_t)gb * p.win_stride, (uint32_t)p.win_stride);
   const uint32_t edge_off = lane < 32 ? span_lo + 4 * lane : span_hi - 128 + 4 * (lane - 32);
   const uint32_t edge_old = __builtin_amdgcn_raw_buffer_load_b32(rrec, edge_off, 0, kStream);
-  if constexpr (kCoal) {
-    if (coal) coalesced_exchange(cx, in, smem, lane);
+  if constexpr (GBF16) {
+    if constexpr (kCoal) {
+      if (coal) coalesced_exchange(cx, in, smem, lane);
+    }
+  } else {
+    // (binary32: loads and exchange in one branch, so that the loaded vectors
+    // are never live together with the other form's)
+    if (coal) {
+      coalesced_load_grad(cx, rg, lane);
+      if constexpr (kCoal) coalesced_exchange(cx, in, smem, lane);
+    } else {
+      lane_load_grad(in, rg, eb);
+    }
   }
 
   // ---------------------------------------------- 1. a = g + Q^-1(e)
   float a[NV][8];
   const int rem = s - (int)eb;  // this lane's elements below the end of the block: [0, rem)
-  if constexpr (LQ) lane_decode_lq(in, lqb, a, rem, full);
-  else lane_decode(in, a, rem, full);
+  if constexpr (LQ && GBF16) {
+    // (a second pass over the straddling runs, as below, spills at five waves
+    // per SIMD: 338 against 260 us per 400 M parameters)
+    lane_decode_lq(in, lqb, a, rem, full);
+  } else if constexpr (LQ) {
+    in.st[0] = lqb.st[0];
+    lane_decode(in, a, rem, full);
+    lane_decode_second<EPL, GBF16, EFM>(a, lqb, re, rg, eb, rem);
+  } else {
+    lane_decode(in, a, rem, full);
+  }
 
   // ---------------------------------------------- 2. Top-K threshold
   float vmax[NV];
@@ -535,7 +566,14 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
         for (int e = 0; e < 8; ++e) {
           const float ab = __builtin_fabsf(a[v][e]);
           if ((ab > tf) | ((ab == tf) & (8 * v + e <= last_here))) {
-            if (pos < (uint32_t)kq) E::store(rw, row0 + pos, E::make(eb + 8 * v + e, a[v][e]));
+            if (pos < (uint32_t)kq) {
+              if constexpr (VF32) {  // (one store of the pair would tie a[] to register pairs)
+                __builtin_amdgcn_raw_buffer_store_b32(eb + 8 * v + e, rw, (row0 + pos) * 8, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(a[v][e]), rw, (row0 + pos) * 8 + 4, 0, 0);
+              } else {
+                E::store(rw, row0 + pos, E::make(eb + 8 * v + e, a[v][e]));
+              }
+            }
             ++pos;
           }
         }
@@ -560,28 +598,35 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
 // 2048 always, since its smaller LDS and registers let six to eight waves per
 // SIMD run where the other form had five (B_d = 1024: 80 -> 60 at k = 11; B_d =
 // 2048: 50 -> 48 at k = 21, 126 -> 52 at k = 103).
-template <int EPL>
+// Binary32 window values keep the search over all elements there (their form
+// of DENSE spills: 372 against 102-126 us at k = 82 and 205).
+template <int EPL, bool VF>
 bool select_dense(int k) {
-  return EPL < 64 || k > 58;
+  return EPL < 64 || (!VF && k > 58);
 }
 
-// LDS bytes of the DENSE form (with 64 elements per lane the block's exchange
-// passes through the same LDS).
-template <int EPL>
-constexpr size_t select_dense_lds() {
-  const size_t w = Dense<EPL>::kLdsWords * 4;
-  return EPL == 64 && w < kTrBytes ? kTrBytes : w;
+// LDS bytes of a select: its lists and row, and with 64 elements per lane the
+// exchange of the block, which passes through the same LDS.
+template <int EPL, bool GB, bool DENSE>
+constexpr size_t select_lds() {
+  const size_t w = DENSE ? Dense<EPL>::kLdsWords * 4 : select_lds_words() * 4;
+  const size_t tr = EPL < 64 ? 0 : GB ? kTrBytes : kTrBytesF32;
+  return w > tr ? w : tr;
 }
 
 template <int EPL, bool LB, bool GB, bool VF, int EFM>
 hipError_t launch_select_t(const StepParams& p, int64_t first, int64_t count, hipStream_t stream) {
   if (count <= 0) return hipSuccess;
-  if (select_dense<EPL>(p.k_full))
-    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM, false, true>), dim3((uint32_t)count), dim3(kWave),
-                       select_dense_lds<EPL>(), stream, p, first, count);
-  else if constexpr (EPL == 64)
-    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM>), dim3((uint32_t)count), dim3(kWave),
-                       select_lds_words() * 4, stream, p, first, count);
+  if (select_dense<EPL, VF>(p.k_full)) {
+    constexpr bool DENSE = EPL < 64 || !VF;
+    const size_t lds = select_lds<EPL, GB, DENSE>();
+    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM, false, DENSE>), dim3((uint32_t)count), dim3(kWave), lds,
+                       stream, p, first, count);
+  } else if constexpr (EPL == 64) {
+    const size_t lds = select_lds<EPL, GB, false>();
+    hipLaunchKernelGGL((select_kernel<EPL, LB, GB, VF, EFM>), dim3((uint32_t)count), dim3(kWave), lds, stream, p, first,
+                       count);
+  }
   return hipGetLastError();
 }
 

@@ -520,7 +520,7 @@ apply_kernel(StepParams p, int64_t first, int64_t count, int32_t nsb) {
   const Rsrc rs = make_rsrc(p.state + p.stats_plane + ((uint64_t)gb * nbk + (uint64_t)sb * sub_bk) * 8, sub_bk * 8);
   constexpr bool kCoal = GBF16;
   LaneIn<EPL, LB, GBF16, EFM> in;
-  CoalescedIn cx;
+  CoalescedIn<GBF16> cx;
   if constexpr (kCoal) {
 #pragma unroll
     for (int v = 0; v < (LB ? 1 : NV); ++v)
