@@ -121,6 +121,11 @@ __device__ __forceinline__ float div15(float d) {
 // bit 1: randomized rounding (Lemma 1) instead of round-to-nearest.
 constexpr int kEf8 = 1, kEfRandom = 2;
 
+// a ^ b ^ c in one instruction (the compiler makes two).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 // Philox4x32-10 (Salmon, Moraes, Dror and Shaw, "Parallel Random Numbers: As
 // Easy as 1, 2, 3", SC 2011): ten rounds of two 32x32 -> 64-bit products
 // with the round keys; the key advances by the Weyl constants between rounds
@@ -135,7 +140,7 @@ __device__ __forceinline__ u32x4 philox4x32_10(u32x4 c, uint32_t k0, uint32_t k1
     // one 32x32 -> 64-bit multiply each (v_mad_u64_u32)
     const uint64_t p0 = (uint64_t)0xD2511F53u * c[0];
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c[2];
-    c = u32x4{(uint32_t)(p1 >> 32) ^ c[1] ^ k0, (uint32_t)p1, (uint32_t)(p0 >> 32) ^ c[3] ^ k1, (uint32_t)p0};
+    c = u32x4{xor3((uint32_t)(p1 >> 32), c[1], k0), (uint32_t)p1, xor3((uint32_t)(p0 >> 32), c[3], k1), (uint32_t)p0};
   }
   return c;
 }
@@ -811,17 +816,47 @@ __device__ __forceinline__ void vector_codes(const float (&x)[8], float mnv, flo
   constexpr int CW = EF8 ? 2 : 1;
   constexpr float L = EF8 ? 255.0f : 15.0f;
   if constexpr ((EFM & kEfRandom) != 0) {
-    // the vector starts at a multiple of 8 within the tensor
+    // The vector starts at a multiple of 8 within the tensor.  t = (x - min)/u
+    // + xi - 1/2 by v_rcp and two FMAs lies within 2^-18 (4-bit codes, t < 16)
+    // or 2^-14 (8-bit, t < 256) of the IEEE quotient plus xi (the reciprocal's
+    // ulp times the largest quotient, and four roundings of half an ulp), and
+    // the code is monotone in t: where t - eps and t + eps round to the same
+    // integer for an eps of twice that, it is the exact floor (a quotient plus
+    // xi that reaches the level after the last one always lies within eps of
+    // it).  Elsewhere (one vector of a wave in 128, or in 9) the lane takes
+    // the exact form with its IEEE divisions.
+    constexpr float kEps = EF8 ? 0x1p-13f : 0x1p-17f;
     uint32_t w24[8];
     philox_w24(quad, st, w24);
+    const float rcp = __builtin_amdgcn_rcpf(uv);
+    uint32_t d1[2] = {}, d2[2] = {};
 #pragma unroll
-    for (int c = 0; c < CW; ++c) w[c] = 0;
-    if (uv != 0.0f) {
+    for (int e = 0; e < 8; ++e) {
+      const float y = __builtin_fmaf(x[e] - mnv, rcp, -0.5f);
+      const float t = __builtin_fmaf((float)w24[e], 0x1p-24f, y);
+      // bytes 0-3: elements 0-3 and 4-7 (8-bit), or the even and the odd ones
+      const int word = EF8 ? e >> 2 : e & 1, byte = EF8 ? e & 3 : e >> 1;
+      d1[word] = __builtin_amdgcn_cvt_pk_u8_f32(t - kEps, byte, d1[word]);  // half to even, clamped to [0, 255]
+      d2[word] = __builtin_amdgcn_cvt_pk_u8_f32(t + kEps, byte, d2[word]);
+    }
+    if constexpr (EF8) {
+      w[0] = d1[0];
+      w[CW - 1] = d1[1];
+    } else {
+      w[0] = d1[0] | (d1[1] << 4);
+    }
+    const bool agree = (d1[0] == d2[0]) & (d1[1] == d2[1]);
+    const bool exact_u = uv >= 0x1p-125f && uv <= 0x1p+125f;
+    if (!exact_u | !agree) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t code = code_randomized(x[e], mnv, uv, L, w24[e]);
-        if constexpr (EF8) w[e >> 2] |= code << (8 * (e & 3));
-        else w[0] |= code << (4 * e);
+      for (int c = 0; c < CW; ++c) w[c] = 0;
+      if (uv != 0.0f) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const uint32_t code = code_randomized(x[e], mnv, uv, L, w24[e]);
+          if constexpr (EF8) w[e >> 2] |= code << (8 * (e & 3));
+          else w[0] |= code << (4 * e);
+        }
       }
     }
   } else {
