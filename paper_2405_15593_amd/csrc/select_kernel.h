@@ -167,9 +167,9 @@ __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], co
   return true;
 }
 
-template <int EPL, bool GBF16, int EFM>
+template <int EPL, bool LB, bool GBF16, int EFM>
 constexpr bool select_coalesced() {
-  return EPL == 64 && (!GBF16 || (EFM & kEf8) == 0);
+  return EPL == 64 && (!GBF16 || (LB && (EFM & kEf8) == 0));
 }
 template <int EPL>
 constexpr int select_waves(bool grad_bf16) {
@@ -212,9 +212,10 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   const bool wide = p.block == CAP;
   // 4096-element blocks load and store the block as contiguous kilobytes and
   // exchange it through LDS (coalesced_exchange); the other shapes load each
-  // lane's run directly, and so do bf16 gradients with 8-bit codes (there the
-  // exchange measured slower: 5.95 vs 5.75 ms on the Llama-2-7B list)
-  constexpr bool kCoal = select_coalesced<EPL, GBF16, EFM>();
+  // lane's run directly, and so do bf16 gradients with 8-bit codes or buckets
+  // below 64 (there the exchange costs spills: per 400 M parameters 419 us
+  // with it and 378 without, and 451 and 384 at B_q = 32)
+  constexpr bool kCoal = select_coalesced<EPL, LB, GBF16, EFM>();
   const bool coal = kCoal && wide;
   LaneIn<EPL, LB, GBF16, EFM> in;
   CoalescedIn<GBF16> cx;

@@ -26,6 +26,8 @@ CASES = {
     "block8192_bucket8195_bf16": dict(block=8192, bucket=8195, **BF),
     "block8192_bucket20011_f32": dict(block=8192, bucket=20011),
     "block12304_bucket15001": dict(block=12304, bucket=15001, **BF),
+    "bf16_bucket32_inside": dict(bucket=32, **BF),
+    "bf16_bucket8_randomized": dict(bucket=8, ef_rounding=1, ef_seed=3, **BF),
     "f32_ef8_inside": dict(ef_bits=8),
     "f32_ef8_bucket8": dict(ef_bits=8, bucket=8),
     "f32_randomized_bucket32": dict(ef_rounding=1, ef_seed=9, bucket=32),
