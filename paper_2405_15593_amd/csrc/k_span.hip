@@ -62,11 +62,10 @@ __global__ void __launch_bounds__(256) bucket_reduce_kernel(StepParams p, int32_
 // segment table.
 //
 // Blocks that are whole sub-blocks come and go as contiguous kilobytes through
-// LDS (coalesced_exchange).  A lane decodes and quantizes with the pairs of its
-// first element's bucket (codes from two bracketing products instead of an IEEE
-// division, as in the select); elements past a bucket's end inside a lane's run
-// are then done again with the next one's (a uniform branch, one block in 24
-// with buckets of 100,000).
+// LDS (coalesced_exchange).  A lane decodes with the pair of its first element's
+// bucket, and elements past a bucket's end inside its run again with the next
+// one's (a uniform branch, one block in 24 with buckets of 100,000).  Codes come
+// from two bracketing products instead of an IEEE division, as in the select.
 // 400 M bf16 parameters: 322 -> 255 us (3.9 TB/s).
 template <bool GBF16, bool VF32, int EFM>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
@@ -153,29 +152,33 @@ requant_kernel(StepParams p, int64_t first, int64_t count, int32_t nsub) {
   lane_decode(in, a, rem, full);
   lane_decode_second<EPL, GBF16, EFM>(a, old_b, re, rg, el, rem);
   zero_kept();
-  const float lo = __uint_as_float(new_b.st[0][0]), u = ef_step<EFM>(__uint_as_float(new_b.st[0][1]) - lo);
+  // each vector with its first element's bucket; the vector that the bucket
+  // ends inside (wherever a lane has one: a uniform branch) again with the next
+  // one, the elements before it at that bucket's lower bound
+  const float lo0 = __uint_as_float(new_b.st[0][0]), u0 = ef_step<EFM>(__uint_as_float(new_b.st[0][1]) - lo0);
+  const float lo1 = __uint_as_float(new_b.st[1][0]), u1 = ef_step<EFM>(__uint_as_float(new_b.st[1][1]) - lo1);
+  const int sp = new_b.sp;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
+    const uint64_t quad = (uint64_t)(b.e0 + eb + 8 * v) >> 2;
+    const float lo = 8 * v >= sp ? lo1 : lo0, u = 8 * v >= sp ? u1 : u0;
     uint32_t c[CW];
-    vector_codes<EFM>(a[v], lo, u, (uint64_t)(b.e0 + eb + 8 * v) >> 2, st, c);
+    vector_codes<EFM>(a[v], lo, u, quad, st, c);
+    if (ballot(sp > 8 * v && sp < 8 * v + 8) != 0) {
+      float x[8];
 #pragma unroll
-    for (int h = 0; h < CW; ++h) wv[CW * v + h] = c[h];
-  }
-  if (ballot(new_b.sp < EPL) != 0) {  // the elements in the lane's second bucket
-    const float lo1 = __uint_as_float(new_b.st[1][0]), u1 = ef_step<EFM>(__uint_as_float(new_b.st[1][1]) - lo1);
-    const int sp = opaque_v(new_b.sp), eo = opaque_v((int)eb);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      __builtin_amdgcn_sched_barrier(0);
-      uint32_t c[CW];
-      vector_codes<EFM>(a[v], lo1, u1, (uint64_t)(b.e0 + eo + 8 * v) >> 2, st, c);
+      for (int e = 0; e < 8; ++e) x[e] = 8 * v + e >= sp ? a[v][e] : lo1;
+      uint32_t c1[CW];
+      vector_codes<EFM>(x, lo1, u1, quad, st, c1);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const uint32_t m = (EFM & kEf8) ? 0xFFu << (8 * (e & 3)) : 0xFu << (4 * e);
-        uint32_t& w0 = wv[(EFM & kEf8) ? CW * v + (e >> 2) : v];
-        if (8 * v + e >= sp) w0 = (w0 & ~m) | (c[(EFM & kEf8) ? e >> 2 : 0] & m);
+        uint32_t& w = c[(EFM & kEf8) ? e >> 2 : 0];
+        if (8 * v + e >= sp) w = (w & ~m) | (c1[(EFM & kEf8) ? e >> 2 : 0] & m);
       }
     }
+#pragma unroll
+    for (int h = 0; h < CW; ++h) wv[CW * v + h] = c[h];
   }
   if (!full) {  // codes past the block's end are 0
     const int r = opaque_v(rem);

@@ -808,7 +808,9 @@ __device__ __forceinline__ void philox_w24(uint64_t quad, const EfStream& st, ui
 // quantization step uv): 4-bit codes in w[0], element e in bits [4e, 4e + 4);
 // 8-bit codes in w[0], w[1], element e in byte e & 3 of word e / 4.  quad:
 // the tensor element number of x[0], divided by 4 (the randomized rounding's
-// counter).
+// counter).  Every x lies in its bucket's range, up to rounding; one that does
+// not (past the end of the tensor or of its bucket) may reach the 4-bit codes
+// of the elements after it in the vector, never of those before.
 template <int EFM>
 __device__ __forceinline__ void vector_codes(const float (&x)[8], float mnv, float uv, uint64_t quad,
                                              const EfStream& st, uint32_t (&w)[(EFM & kEf8) ? 2 : 1]) {
