@@ -62,11 +62,15 @@ __global__ void __launch_bounds__(256) bucket_reduce_kernel(StepParams p, int32_
 // segment table.
 //
 // Blocks that are whole sub-blocks come and go as contiguous kilobytes through
-// LDS (coalesced_exchange).  A lane decodes with the pair of its first element's
-// bucket, and elements past a bucket's end inside its run again with the next
-// one's (a uniform branch, one block in 24 with buckets of 100,000).  Codes come
-// from two bracketing products instead of an IEEE division, as in the select.
-// 400 M bf16 parameters: 322 -> 255 us (3.9 TB/s).
+// LDS (coalesced_exchange).  Decode and codes take a vector at a time with its
+// first element's bucket, and only a vector that holds a bucket's end again with
+// the next one (a uniform branch per vector); codes come from two bracketing
+// products instead of an IEEE division, as in the select.
+// All of a step but its update, 64 M bf16 parameters, with an IEEE division per
+// element and uncoalesced accesses, and now: B_q = 100,000 141 -> 113 us, B_q =
+// 5003 (a bucket's end in four blocks of five) 128 -> 114.  (Decoding and
+// quantizing the whole block a second time where a run straddles: 132 and 216;
+// the reloaded inputs of that decode took 53 to 63 registers to scratch.)
 template <bool GBF16, bool VF32, int EFM>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 requant_kernel(StepParams p, int64_t first, int64_t count, int32_t nsub) {
@@ -148,9 +152,7 @@ requant_kernel(StepParams p, int64_t first, int64_t count, int32_t nsub) {
         a[v][e] = __uint_as_float(__float_as_uint(a[v][e]) & ~(uint32_t)m);
       }
   };
-  in.st[0] = old_b.st[0];
-  lane_decode(in, a, rem, full);
-  lane_decode_second<EPL, GBF16, EFM>(a, old_b, re, rg, el, rem);
+  lane_decode_lq<false>(in, old_b, a, rem, full);
   zero_kept();
   // each vector with its first element's bucket; the vector that the bucket
   // ends inside (wherever a lane has one: a uniform branch) again with the next

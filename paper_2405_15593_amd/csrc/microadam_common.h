@@ -703,25 +703,39 @@ __device__ __forceinline__ LqBuckets lq_buckets(const StepParams& p, const Block
   return r;
 }
 
-// a = g + Q^-1(e) with the lane's two buckets (the arithmetic of lane_decode).
-template <int EPL, bool GBF16, int EFM>
+// a = g + Q^-1(e) with the lane's two buckets (the arithmetic of lane_decode):
+// with EACH every element picks its bucket's pair; without, every vector takes
+// its first element's, and the elements past a bucket's end inside a vector are
+// done again with the next one (a uniform branch per vector, taken where some
+// lane has such an end).
+template <bool EACH, int EPL, bool GBF16, int EFM>
 __device__ __forceinline__ void lane_decode_lq(const LaneIn<EPL, true, GBF16, EFM>& in, const LqBuckets& bk,
                                                float (&a)[EPL / 8][8], int rem, bool full) {
   constexpr int NV = EPL / 8;
   const float lo0 = __uint_as_float(bk.st[0][0]), u0 = ef_step<EFM>(__uint_as_float(bk.st[0][1]) - lo0);
   const float lo1 = __uint_as_float(bk.st[1][0]), u1 = ef_step<EFM>(__uint_as_float(bk.st[1][1]) - lo1);
+  const int sp = bk.sp;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
+    const float lo = 8 * v >= sp ? lo1 : lo0, u = 8 * v >= sp ? u1 : u0;
     float g[8], c[8];
     unpack8<GBF16>(in.graw[v], g);
     unpack_codes<EFM>(in.cw, v, c);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const bool second = 8 * v + e >= bk.sp;
-      const float lo = second ? lo1 : lo0, u = second ? u1 : u0;
-      const float sc = c[e] * u;
-      const float d = sc + lo;
+      const bool second = 8 * v + e >= sp;
+      const float sc = c[e] * (EACH ? (second ? u1 : u0) : u);
+      const float d = sc + (EACH ? (second ? lo1 : lo0) : lo);
       a[v][e] = g[e] + d;
+    }
+    if (!EACH && ballot(sp > 8 * v && sp < 8 * v + 8) != 0) {
+#pragma unroll
+      for (int e = 1; e < 8; ++e) {
+        const float sc = c[e] * u1;
+        const float d = sc + lo1;
+        const float x = g[e] + d;
+        if (8 * v + e >= sp) a[v][e] = x;
+      }
     }
   }
   if (!full) {
@@ -732,44 +746,6 @@ __device__ __forceinline__ void lane_decode_lq(const LaneIn<EPL, true, GBF16, EF
       for (int e = 0; e < 8; ++e)
         if (8 * v + e >= r) a[v][e] = 0.0f;
   }
-}
-
-// The lanes' elements in their second bucket, after a decode of all with the
-// first one's pair: only where some lane's run straddles two buckets (a
-// uniform branch, one block in 24 with buckets of 100,000), with the inputs
-// loaded again, vector by vector, so that they need not stay in registers.
-// re, rg: codes and gradient, the lane's run starting at element eb of both.
-template <int EPL, bool GBF16, int EFM>
-__device__ __forceinline__ void lane_decode_second(float (&a)[EPL / 8][8], const LqBuckets& bk, Rsrc re, Rsrc rg,
-                                                   uint32_t eb, int rem) {
-  if (ballot(bk.sp < EPL) == 0) return;
-  const float lo = __uint_as_float(bk.st[1][0]), u = ef_step<EFM>(__uint_as_float(bk.st[1][1]) - lo);
-  const int sp = opaque_v(bk.sp), r = opaque_v(rem);
-  eb = (uint32_t)opaque_v((int)eb);  // (not merged with the first loads)
-#pragma unroll
-  for (int v = 0; v < EPL / 8; ++v) {
-    __builtin_amdgcn_sched_barrier(0);  // one vector's inputs at a time
-    const Raw8<GBF16> raw = load8<GBF16>(rg, eb + 8 * v);
-    uint32_t cw[2] = {};
-    if constexpr (EFM & kEf8) {
-      const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(re, eb + 8 * v, 0, 0);
-      cw[0] = t[0];
-      cw[1] = t[1];
-    } else {
-      cw[0] = __builtin_amdgcn_raw_buffer_load_b32(re, (eb >> 1) + 4 * v, 0, 0);
-    }
-    float g[8], c[8];
-    unpack8<GBF16>(raw, g);
-    unpack_codes<EFM>(cw, 0, c);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float sc = c[e] * u;
-      const float d = sc + lo;
-      const float x = g[e] + d;
-      if ((8 * v + e >= sp) & (8 * v + e < r)) a[v][e] = x;
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);
 }
 
 template <int EPL>

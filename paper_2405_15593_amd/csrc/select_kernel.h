@@ -271,14 +271,12 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   // ---------------------------------------------- 1. a = g + Q^-1(e)
   float a[NV][8];
   const int rem = s - (int)eb;  // this lane's elements below the end of the block: [0, rem)
-  if constexpr (LQ && GBF16) {
-    // (a second pass over the straddling runs, as below, spills at five waves
-    // per SIMD: 338 against 260 us per 400 M parameters)
-    lane_decode_lq(in, lqb, a, rem, full);
-  } else if constexpr (LQ) {
-    in.st[0] = lqb.st[0];
-    lane_decode(in, a, rem, full);
-    lane_decode_second<EPL, GBF16, EFM>(a, lqb, re, rg, eb, rem);
+  if constexpr (LQ) {
+    // a pair per element but in the form that spills least with a pair per
+    // vector (24 registers against 69); elsewhere the branches of that one cost
+    // registers (bf16: 8 -> 56 spilled, 115 -> 135 us per 64 M parameters)
+    constexpr bool EACH = GBF16 || DENSE || (EFM & kEf8) == 0;
+    lane_decode_lq<EACH>(in, lqb, a, rem, full);
   } else {
     lane_decode(in, a, rem, full);
   }

@@ -85,7 +85,7 @@ __device__ __forceinline__ void select_large_block(const StepParams& p, int64_t 
   // ---------------------------------------------- 1. a = g + Q^-1(e)
   float a[NV][8];
   const int rem = s - (int)eb;
-  if constexpr (LQ) lane_decode_lq(in, lqb, a, rem, full);
+  if constexpr (LQ) lane_decode_lq<false>(in, lqb, a, rem, full);
   else lane_decode(in, a, rem, full);
 
   // workgroup sum of one value per wave; `buf` alternates between calls
