@@ -167,13 +167,21 @@ __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], co
   return true;
 }
 
-template <int EPL, bool LB, bool GBF16, int EFM>
+// Whether 4096-element blocks load and store as contiguous kilobytes and
+// exchange them through LDS (coalesced_exchange); the other shapes load each
+// lane's run directly.  So do the forms in which the exchange takes registers
+// to scratch and gives less than that costs (select in us, with and without):
+// bf16 gradients with 8-bit codes (per 400 M parameters 419 and 378) or buckets
+// below 64 (451 and 384 at B_q = 32); binary32 gradients with 8-bit codes and
+// buckets below 64 (per 64 M parameters 135 and 116 at B_q = 32, 181 and 151 at
+// 8) or spanning blocks (with the two passes after it 167 and 169 at k = 41, 184
+// and 178 at 205).  Binary32 gains from it with 4-bit codes (68 and 95 at B_q =
+// 64, 92 and 102 at 16, the same at 8) and with 8-bit codes in buckets of 64 and
+// more (85 and 106).
+template <int EPL, bool LB, bool GBF16, int EFM, bool LQ>
 constexpr bool select_coalesced() {
-  return EPL == 64 && (!GBF16 || (LB && (EFM & kEf8) == 0));
-}
-template <int EPL>
-constexpr int select_waves(bool grad_bf16) {
-  return EPL == 16 ? 8 : EPL == 32 ? 6 : grad_bf16 ? 5 : 4;
+  constexpr bool ef8 = (EFM & kEf8) != 0;
+  return EPL == 64 && (GBF16 ? LB && !ef8 : !ef8 || (LB && !LQ));
 }
 
 // Five waves per SIMD (96 registers; the kernel's 7.9 KB of LDS lets 20
@@ -182,7 +190,13 @@ constexpr int select_waves(bool grad_bf16) {
 // Binary32 gradients take four: the loaded half of a block and the lane's 64
 // elements need 125 registers (per 1e9 parameters 1353 us with each lane
 // loading its own 256-byte run, five waves; 944 us coalesced through LDS,
-// 5.7 TB/s).
+// 5.7 TB/s), and the directly loading forms 110 to 122 (64 M parameters with
+// 8-bit codes, B_q = 32: 131 us at five waves with 15 to 45 spilled, 116 at
+// four with none).
+template <int EPL>
+constexpr int select_waves(bool grad_bf16) {
+  return EPL == 16 ? 8 : EPL == 32 ? 6 : grad_bf16 ? 5 : 4;
+}
 template <int EPL, bool LB, bool GBF16, bool VF32, int EFM, bool LQ = false, bool DENSE = false>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(select_waves<EPL>(GBF16))))
 select_kernel(StepParams p, int64_t first, int64_t count) {
@@ -210,12 +224,7 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   const Rsrc re = make_rsrc(p.state + p.ef_plane + (uint64_t)gb * ef_bytes, ef_bytes);
   const Rsrc rs = make_rsrc(p.state + p.stats_plane + (uint64_t)gb * nbk * 8, nbk * 8);
   const bool wide = p.block == CAP;
-  // 4096-element blocks load and store the block as contiguous kilobytes and
-  // exchange it through LDS (coalesced_exchange); the other shapes load each
-  // lane's run directly, and so do bf16 gradients with 8-bit codes or buckets
-  // below 64 (there the exchange costs spills: per 400 M parameters 419 us
-  // with it and 378 without, and 451 and 384 at B_q = 32)
-  constexpr bool kCoal = select_coalesced<EPL, LB, GBF16, EFM>();
+  constexpr bool kCoal = select_coalesced<EPL, LB, GBF16, EFM, LQ>();
   const bool coal = kCoal && wide;
   LaneIn<EPL, LB, GBF16, EFM> in;
   CoalescedIn<GBF16> cx;
@@ -272,11 +281,9 @@ select_kernel(StepParams p, int64_t first, int64_t count) {
   float a[NV][8];
   const int rem = s - (int)eb;  // this lane's elements below the end of the block: [0, rem)
   if constexpr (LQ) {
-    // a pair per element but in the form that spills least with a pair per
-    // vector (24 registers against 69); elsewhere the branches of that one cost
-    // registers (bf16: 8 -> 56 spilled, 115 -> 135 us per 64 M parameters)
-    constexpr bool EACH = GBF16 || DENSE || (EFM & kEf8) == 0;
-    lane_decode_lq<EACH>(in, lqb, a, rem, full);
+    // (a pair per vector: its branches take 56 registers to scratch with bf16
+    // gradients, 135 against 115 us per 64 M parameters)
+    lane_decode_lq<true>(in, lqb, a, rem, full);
   } else {
     lane_decode(in, a, rem, full);
   }

@@ -44,3 +44,22 @@ def test_span_edges(name):
     for _ in range(4):
         run.step(check_moments=False)
     run.opt.close()
+
+
+# binary32 gradients with 8-bit codes: the forms that load each lane's run
+# directly (buckets below 64, buckets spanning blocks), at sparse and dense rows
+@pytest.mark.parametrize("kw", [
+    dict(bucket=8, density=0.05),
+    dict(bucket=16, density=0.05, value_f32=True),
+    dict(bucket=32, ef_rounding=1, ef_seed=12),
+    dict(bucket=32, density=0.05, ef_rounding=1, ef_seed=13),
+    dict(bucket=4099, density=0.05),
+    dict(bucket=5003, value_f32=True),
+], ids=str)
+def test_f32_ef8_direct(kw):
+    test_args = dict(dict(window=3, density=0.01, ef_bits=8), **kw)
+    print(f"[f32 ef8 direct] {test_args}", flush=True)
+    run = GpuOracleRun([5 * 4096 + 1237, 4096, 501], **test_args)
+    for _ in range(4):
+        run.step(check_moments=False)
+    run.opt.close()
