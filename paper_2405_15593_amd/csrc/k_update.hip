@@ -44,14 +44,21 @@ __device__ __forceinline__ uint32_t zswap(uint32_t i) {
   return PBF16 ? i ^ ((i >> 4) & 4u) : i;
 }
 
-// lr * (c1 s1) / (eps + sqrt(c2 s2)).  One Newton step with the exact residual
-// after v_rsq_f32 and v_rcp_f32 (each within 1 ulp) gives the correctly rounded
-// root and quotient but for a rare last-place miss, in a third of the
-// instructions of the library forms; those take the arguments outside the
-// range where no intermediate of the step can under- or overflow (and zeros,
-// infinities and NaN).  eps_ok: eps itself lies in that range (uniform).
-constexpr uint32_t kRangeLo = 0x0D800000u, kRangeHi = 0x71800000u;  // 2^-100, 2^100
-__device__ __forceinline__ bool range_ok(float x) { return __float_as_uint(x) - kRangeLo <= kRangeHi - kRangeLo; }
+// lr * (c1 s1) / (eps + sqrt(c2 s2)), the root and the quotient correctly
+// rounded in under half of the instructions of the library forms.  After v_rsq
+// one Newton step with the exact residual gives the rounded root, and after
+// v_rcp one gives the rounded reciprocal (both checked against the IEEE results
+// for every float of the ranges below); a quotient from a rounded reciprocal and
+// one exact residual is the rounded quotient (Markstein, "Computation of
+// elementary functions on the IBM RISC System/6000 processor", 1990).  The
+// library forms take the arguments outside the range in which no residual or
+// result can under- or overflow (and zeros, infinities and NaN): vh and |mh| in
+// [2^-100, 2^50], eps up to 2^24 (uniform).
+__device__ __forceinline__ bool range_ok(float mh, float vh) {
+  const float a = __builtin_fabsf(mh);
+  return (__builtin_fminf(a, vh) >= 0x1p-100f) & (__builtin_fmaxf(a, vh) <= 0x1p50f);
+}
+__device__ __forceinline__ bool range_eps(float x) { return x <= 0x1p24f; }
 __device__ __forceinline__ float decrement(const StepParams& p, float s1, float s2, bool eps_ok) {
   const float mh = p.c1 * s1;
   const float vh = p.c2 * s2;
@@ -59,10 +66,11 @@ __device__ __forceinline__ float decrement(const StepParams& p, float s1, float 
   const float q = vh * r;
   const float root = __builtin_fmaf(__builtin_fmaf(-q, q, vh), 0.5f * r, q);
   const float den = p.eps + root;
-  const float y = __builtin_amdgcn_rcpf(den);
+  const float y0 = __builtin_amdgcn_rcpf(den);
+  const float y = __builtin_fmaf(__builtin_fmaf(-den, y0, 1.0f), y0, y0);
   const float d0 = mh * y;
   float d = __builtin_fmaf(__builtin_fmaf(-d0, den, mh), y, d0);
-  if (!range_ok(vh) | !eps_ok) d = mh / (p.eps + __builtin_sqrtf(vh));
+  if (!range_ok(mh, vh) | !eps_ok) d = mh / (p.eps + __builtin_sqrtf(vh));
   return p.lr * d;
 }
 
@@ -252,7 +260,7 @@ update_kernel(StepParams p, int64_t first_block, int64_t count) {
   if (lead) rebuild(w2s, BoolTag<true>{});
   lds_sync();
   {
-    const bool eps_ok = range_ok(p.eps);
+    const bool eps_ok = range_eps(p.eps);
     const int nn = opaque(n);
 #pragma unroll
     for (int i = 0; i < KS; ++i)
@@ -328,7 +336,7 @@ __global__ void __launch_bounds__(NT) update_rows_kernel(StepParams p, int64_t f
     }
     if (!EXPORT) {
       // one 64-entry chunk at a time; z2 = -1 marks a converted word
-      const bool eps_ok = range_ok(p.eps);
+      const bool eps_ok = range_eps(p.eps);
       for (int row = 0, slot = slot0; row < n_live; ++row, slot = (slot + 1 == m) ? 0 : slot + 1)
         for (int jj = lane; jj < kq; jj += kWave) {
           const uint32_t i = E::idx(E::load(rw, slot * kq + jj));
