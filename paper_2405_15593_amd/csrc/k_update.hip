@@ -59,7 +59,7 @@ __device__ __forceinline__ bool range_ok(float mh, float vh) {
   return (__builtin_fminf(a, vh) >= 0x1p-100f) & (__builtin_fmaxf(a, vh) <= 0x1p50f);
 }
 __device__ __forceinline__ bool range_eps(float x) { return x <= 0x1p24f; }
-__device__ __forceinline__ float decrement(const StepParams& p, float s1, float s2, bool eps_ok) {
+__device__ __forceinline__ float decrement_in_range(const StepParams& p, float s1, float s2, bool eps_ok, bool& ok) {
   const float mh = p.c1 * s1;
   const float vh = p.c2 * s2;
   const float r = __builtin_amdgcn_rsqf(vh);
@@ -69,9 +69,16 @@ __device__ __forceinline__ float decrement(const StepParams& p, float s1, float 
   const float y0 = __builtin_amdgcn_rcpf(den);
   const float y = __builtin_fmaf(__builtin_fmaf(-den, y0, 1.0f), y0, y0);
   const float d0 = mh * y;
-  float d = __builtin_fmaf(__builtin_fmaf(-d0, den, mh), y, d0);
-  if (!range_ok(mh, vh) | !eps_ok) d = mh / (p.eps + __builtin_sqrtf(vh));
-  return p.lr * d;
+  ok = range_ok(mh, vh) & eps_ok;
+  return p.lr * __builtin_fmaf(__builtin_fmaf(-d0, den, mh), y, d0);
+}
+__device__ __forceinline__ float decrement_any(const StepParams& p, float s1, float s2) {
+  return p.lr * ((p.c1 * s1) / (p.eps + __builtin_sqrtf(p.c2 * s2)));
+}
+__device__ __forceinline__ float decrement(const StepParams& p, float s1, float s2, bool eps_ok) {
+  bool ok;
+  const float d = decrement_in_range(p, s1, s2, eps_ok, ok);
+  return ok ? d : decrement_any(p, s1, s2);
 }
 
 // theta <- theta * decay - decrement over a thread's parameter vectors, the
@@ -246,15 +253,20 @@ update_kernel(StepParams p, int64_t first_block, int64_t count) {
   // second sums start from it like from 0; a sum that started at +0 is never
   // -0).  Of the entries of one element the first to come gets the sum and
   // turns the two sums into the decrement; the others get -0 and are done.
+  // (Lanes without an entry stay out: exchanges of one word, the sink, follow
+  // each other.)
   constexpr uint32_t kTaken = 0x80000000u;
   uint32_t s1[KS];
   {
     const int nn = opaque(n);
 #pragma unroll
     for (int i = 0; i < KS; ++i)
-      if (i * NT < nn)
-        s1[i] = __hip_atomic_exchange((LdsWord*)(uintptr_t)zp[i], kTaken, __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (i * NT < nn) {
+        s1[i] = kTaken;
+        if (zp[i] != sink)
+          s1[i] = __hip_atomic_exchange((LdsWord*)(uintptr_t)zp[i], kTaken, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
   }
   lds_sync();
   if (lead) rebuild(w2s, BoolTag<true>{});
@@ -270,6 +282,92 @@ update_kernel(StepParams p, int64_t first_block, int64_t count) {
   lds_sync();
 
   apply_decrements<NT, PBF16>(p, rp, th, z, tid, s);
+}
+
+// Blocks of one wave (up to 1024 elements) with few and long rows (the rule is
+// at the launch): lane l holds entry l of every live row, oldest first, in
+// registers, and no entry passes through a stage.  Each row (distinct words)
+// adds to the accumulator in one LDS round trip; rows past the live ones and
+// lanes past the row's end add to the sink.  Every entry reads both its sums
+// before any word is overwritten, so the entries of one element write the same
+// decrement.  All of it is one straight run over KR rows: in a small launch
+// that run's latency is the time.  Through the stage and held, update in us,
+// B_d = 1024, k = 52, m = 10:
+//   bf16      64 M parameters 82 -> 69   1 M 8.9 -> 6.9
+//   binary32                             1 M 9.0 -> 6.9
+template <bool PBF16, bool VF32, int KR>
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8)))
+update_held_kernel(StepParams p, int64_t first_block, int64_t count) {
+  constexpr int NT = kWave, CAP = NT * kLaneElems;
+  using E = Entry<VF32>;
+  using ET = typename E::T;
+  using V = Vec16<PBF16>;
+  extern __shared__ __align__(16) uint32_t smem[];
+  float* const z = (float*)smem;
+
+  const int lane = thread_id();
+  const int m = p.window, n_live = p.n_live;
+  const Span u = span_of(p, (int32_t)(first_block + xcd_block(block_id(), count)), PBF16 ? 2 : 4);
+  const int s = u.s, kq = u.kq;
+  const Rsrc rw = window_rsrc<VF32 ? 2 : 1>(p, u.gb, kq);
+  ET w[KR];
+  int slot = (p.new_slot + 1 + m - n_live) % m;  // the oldest live row
+#pragma unroll
+  for (int i = 0; i < KR; ++i) {  // (rows past the live ones: any rows of the record)
+    w[i] = E::template load<kStream>(rw, (uint32_t)(slot * kq + lane));
+    if (++slot == m) slot = 0;
+  }
+  const Rsrc rp = make_rsrc((const void*)u.base, vec_bytes<PBF16>(s));
+  u32x4 th[V::NV];
+#pragma unroll
+  for (int v = 0; v < V::NV; ++v) th[v] = V::load(rp, V::template first<NT>(v, lane));
+  const float w1s = constant_ptr(p.wpow)[lane];  // kMaxWindow is one wave's lanes
+  const float w2s = constant_ptr(p.wpow)[kMaxWindow + lane];
+  {
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *(float4*)(z + q * 4 * NT + lane * 4) = zero;
+  }
+  uint32_t zp[KR];  // the entry's accumulator word
+#pragma unroll
+  for (int i = 0; i < KR; ++i) {
+    const uint32_t idx = E::word(w[i]);
+    zp[i] = (i < n_live) & (lane < kq) & (idx < (uint32_t)s) ? zswap<PBF16>(idx) : (uint32_t)CAP;
+  }
+  wave_sync();
+
+  auto rebuild = [&](float ws, bool sq) {
+#pragma unroll
+    for (int i = 0; i < KR; ++i) {
+      const float wr =
+          __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ws), (n_live - 1 - i) & (kMaxWindow - 1)));
+      const float v = E::val(w[i]);
+      z[zp[i]] = z[zp[i]] + wr * (sq ? v * v : v);
+    }
+  };
+  float s1[KR], d[KR];
+  rebuild(w1s, false);
+#pragma unroll
+  for (int i = 0; i < KR; ++i) s1[i] = z[zp[i]];
+#pragma unroll
+  for (int i = 0; i < KR; ++i) z[zp[i]] = 0.0f;
+  rebuild(w2s, true);
+  const bool eps_ok = range_eps(p.eps);
+  bool out = false;  // an entry outside the range
+#pragma unroll
+  for (int i = 0; i < KR; ++i) {
+    bool ok;
+    d[i] = decrement_in_range(p, s1[i], z[zp[i]], eps_ok, ok);
+    out |= !ok & (zp[i] != (uint32_t)CAP);
+  }
+  if (ballot(out) != 0) {
+#pragma unroll
+    for (int i = 0; i < KR; ++i) d[i] = decrement_any(p, s1[i], z[zp[i]]);
+  }
+#pragma unroll
+  for (int i = 0; i < KR; ++i) z[zp[i]] = d[i];
+  wave_sync();
+  apply_decrements<NT, PBF16>(p, rp, th, z, lane, s);
 }
 
 // Debug export, and the update where the live rows do not fit the stage (more
@@ -391,6 +489,32 @@ bool fits_stage(const StepParams& p) {
   return n <= (int64_t)kStageMax * NT && staged_lds_bytes<NT, VF>((int)n) <= 65536;
 }
 
+// Blocks of one wave with rows of 25 to 64 entries: held in registers, up to 13
+// live rows with bf16 parameters and up to 10 with binary32 ones (more take
+// registers to scratch: bf16, 16 rows, k = 33, 43 against 34 us per 16.8 M
+// parameters).  Shorter rows leave most of every held access empty, and the
+// stage's flat accesses win (B_d = 1024, m = 10, 64 M bf16 parameters: k = 11 59
+// against 52 us, k = 21 the same, k = 26 66 against 71).  Binary32 parameters
+// only in launches that leave the chip's 8192 wave slots unfilled, where one
+// block's latency counts: 64 M parameters, k = 41, take 111 us held and 109
+// through the stage, 300,000 take 6.3 and 7.5.  Returns false elsewhere.
+template <bool PB, bool VF>
+bool launch_update_held(const StepParams& p, int64_t first, int64_t count, hipStream_t stream, hipError_t& err) {
+  if (p.k_full <= 24 || p.k_full > kWave || p.n_live > (PB ? 13 : 10) || (!PB && count > 8192)) return false;
+  auto go = [&](auto kr) {
+    hipLaunchKernelGGL((update_held_kernel<PB, VF, decltype(kr)::value>), dim3((uint32_t)count), dim3(kWave),
+                       (staged_lds_bytes<kWave, VF>(0)), stream, p, first, count);
+    err = hipGetLastError();
+    return true;
+  };
+  if (p.n_live <= 4) return go(std::integral_constant<int, 4>{});
+  if (p.n_live <= 7) return go(std::integral_constant<int, 7>{});
+  if constexpr (PB) {
+    if (p.n_live > 10) return go(std::integral_constant<int, 13>{});
+  }
+  return go(std::integral_constant<int, 10>{});
+}
+
 // The staged kernel wherever every block's live rows fit the stage, else row
 // by row (a stage of more entries leaves one or two workgroups per compute
 // unit; m * k above 6144 at B_d = 4096 lies outside the method's settings).
@@ -402,6 +526,10 @@ hipError_t launch_update_t(const StepParams& p, int64_t first, int64_t count, hi
     hipLaunchKernelGGL((update_rows_kernel<NT, PB, VF, false>), dim3((uint32_t)count), dim3(NT), lds, stream, p, first,
                        count, (float*)nullptr, (float*)nullptr);
     return hipGetLastError();
+  }
+  if constexpr (NT == kWave) {
+    hipError_t err;
+    if (launch_update_held<PB, VF>(p, first, count, stream, err)) return err;
   }
   const int ks = (p.n_live * p.k_full + NT - 1) / NT;
   if (ks <= 2) return launch_update_k<NT, PB, VF, 2>(p, first, count, stream);

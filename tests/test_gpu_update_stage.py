@@ -48,3 +48,46 @@ def test_update_stage(name):
     for _ in range(kw["window"] + 2):
         run.step(check_moments=run.t % 7 == 0)
     run.opt.close()
+
+
+# blocks of one wave with rows of 25 to 64 entries, held in registers: the rule's
+# edges in k, live rows (4, 7, 10 and 13 at most) and types, and both sides of it
+HELD = {
+    "k24_window4": dict(density=24 / 1024, window=4),
+    "k25_window4": dict(density=25 / 1024, window=4),
+    "k64_window5": dict(density=64 / 1024, window=5, param_dtype=bf16),
+    "k64_window7_f32_values": dict(density=64 / 1024, window=7, value_f32=True),
+    "k65_window7": dict(density=65 / 1024, window=7),
+    "k41_window8": dict(density=41 / 1024, window=8),
+    "k52_window10": dict(density=0.05, window=10),
+    "k52_window11_f32": dict(density=0.05, window=11),
+    "k52_window11_bf16": dict(density=0.05, window=11, param_dtype=bf16),
+    "k52_window13_f32_values": dict(density=0.05, window=13, param_dtype=bf16, value_f32=True),
+    "k52_window14": dict(density=0.05, window=14, param_dtype=bf16),
+    "ties": dict(density=0.05, window=6, grad_dist="signs", grad_scale=1e-2, degenerate=True),
+    "zero_values": dict(density=0.05, window=3, grad_dist="sparse_spikes", degenerate=True),
+    "outside_the_range": dict(density=0.05, window=3, grad_scale=1e-16, eps=1e-20),
+    "block512_k26_window10": dict(block=512, density=0.05, window=10, param_dtype=bf16, weight_decay=0.1),
+    "block1008_bucket16": dict(block=1008, bucket=16, density=0.04, window=9),
+}
+
+
+@pytest.mark.parametrize("name", HELD)
+def test_update_held(name):
+    kw = dict(dict(block=1024), **HELD[name])
+    print(f"[update held] {name} {kw}", flush=True)
+    run = GpuOracleRun([5 * kw["block"] + 700, 33, kw["block"]], **kw)
+    for _ in range(kw["window"] + 2):
+        run.step(check_moments=False)
+    run.opt.close()
+
+
+def test_update_many_blocks_f32():
+    """Binary32 parameters in 8192 and 8193 blocks, the two sides of the rule."""
+    for blocks in (8192, 8193):
+        print(f"[update held] {blocks} blocks", flush=True)
+        run = GpuOracleRun([512 * blocks - 12], block=512, density=26 / 512, window=3,
+                           sample=lambda j, nb: (0, 1, nb // 2, nb - 1))
+        for _ in range(4):
+            run.step(check_moments=False)
+        run.opt.close()
