@@ -70,3 +70,71 @@ def test_nonfinite_blocks_are_isolated(block, bucket, density, window):
     assert torch.equal(p_bad[0][good].view(torch.int16), p_ok[0][good].view(torch.int16))
     for x, y in zip(m_bad[0], m_ok[0]):
         assert torch.equal(x[good].view(torch.int32), y[good].view(torch.int32))
+
+
+# the forms that the cases above do not reach: dense rows (k above 58) and blocks
+# of up to 2048 elements (vector maxima, the short blocks' updates), binary32
+# gradients (their exchange and direct loads), 8-bit and randomized codes
+FORMS = {
+    "k205": dict(density=0.05),
+    "k205_f32": dict(density=0.05, grad="f32"),
+    "k385_all_elements": dict(density=385 / 4096),
+    "f32": dict(grad="f32"),
+    "f32_ef8": dict(grad="f32", ef_bits=8),
+    "f32_ef8_bucket16": dict(grad="f32", ef_bits=8, ef_bucket=16),
+    "f32_values": dict(density=0.05, grad="f32", value_f32=True),
+    "ef8": dict(ef_bits=8),
+    "randomized": dict(ef_rounding=1),
+    "randomized8_f32": dict(grad="f32", ef_rounding=1, ef_bits=8),
+    "block1024": dict(topk_block=1024),
+    "block1024_k52": dict(topk_block=1024, density=0.05),
+    "block1024_k52_f32_randomized": dict(topk_block=1024, density=0.05, grad="f32", ef_rounding=1),
+    "block2048_k103": dict(topk_block=2048, density=0.05),
+    "block512": dict(topk_block=512, ef_bucket=8),
+}
+
+
+@pytest.mark.parametrize("name", FORMS)
+def test_nonfinite_forms(name):
+    import torch
+    dev = torch.device("cuda:0")
+    kw = dict(FORMS[name])
+    gdt = torch.float32 if kw.pop("grad", "bf16") == "f32" else torch.bfloat16
+    if kw.pop("value_f32", False):
+        kw["window_value_dtype"] = ma.MICROADAM_F32
+    block, window, steps = kw.get("topk_block", 4096), 4, 6
+    numels = [block * 7 + 1000 % block, block + 33]
+    bad = {1: ["nan"], 3: ["inf", "-inf"], 5: ["nan"] * (block - 3), 7: ["nan"]}  # block 5: 3 finite values left
+    gen = torch.Generator(device="cpu").manual_seed(23)
+    grads = {"bad": [], "clean": []}
+    for _ in range(steps):
+        a, b = (torch.randn(n, generator=gen) * 1e-3 for n in numels)
+        clean = a.clone()
+        for q, values in bad.items():
+            at = slice(q * block + 2, q * block + 2 + len(values))
+            a[at] = torch.tensor([float(v) for v in values])
+            clean[at] = 0.0
+        for key, x in (("bad", a), ("clean", clean)):
+            grads[key].append([x.to(dev, gdt), b.to(dev, gdt)])
+
+    def run(gs):
+        pg = torch.Generator(device="cpu").manual_seed(5)
+        params = [(torch.randn(n, generator=pg) * 0.02).to(dev, torch.bfloat16) for n in numels]
+        opt = ma.MicroAdam(params, ma.make_config(**dict(dict(window=window, lr=1e-3, seed=9), **kw)))
+        for g in gs:
+            opt.step(g)
+        torch.cuda.synchronize()
+        moments = [opt.debug_moments(j) for j in range(2)]
+        opt.close()
+        return params, moments
+
+    print(f"[nonfinite forms] {name} {kw} {gdt}", flush=True)
+    p_bad, m_bad = run(grads["bad"])
+    p_ok, m_ok = run(grads["clean"])
+    good = [torch.ones(n, dtype=torch.bool, device=dev) for n in numels]
+    for q in bad:
+        good[0][q * block:(q + 1) * block] = False
+    for j in range(2):
+        assert torch.equal(p_bad[j][good[j]], p_ok[j][good[j]])
+        for x, y in zip(m_bad[j], m_ok[j]):
+            assert torch.equal(x[good[j]].view(torch.int32), y[good[j]].view(torch.int32))
