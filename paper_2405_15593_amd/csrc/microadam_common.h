@@ -159,13 +159,6 @@ __device__ __forceinline__ uint32_t code_randomized(float x, float lo, float u, 
   return (uint32_t)r;
 }
 
-// Round-to-nearest code (Algorithm 2, Q): rint((x - lo)/u) with an IEEE
-// division, clamped to [0, L].  u != 0.
-__device__ __forceinline__ uint32_t code_nearest(float x, float lo, float u, float levels) {
-  const float r = __builtin_rintf((x - lo) / u);
-  return (uint32_t)__builtin_fminf(__builtin_fmaxf(r, 0.0f), levels);
-}
-
 // Quantization step of a bucket: (max - min) / L, correctly rounded.
 template <int EFM>
 __device__ __forceinline__ float ef_step(float d) {
@@ -523,8 +516,12 @@ __device__ __forceinline__ Rsrc window_rsrc(const StepParams& p, int64_t gb, int
 //   2. the vectors holding some |a| >= L are gathered in LDS, and their
 //      elements >= L (the candidates, in element order) compacted;
 //   3. the k-th largest key among the candidates, bit by bit from the top.
-// Blocks where a stage overflows its LDS (or k > 128) take an exact bitwise
-// search over all elements instead.
+// Rows of more than 58 entries with bf16 window values, and every block of up
+// to 2048 elements, take the bound from the maxima of all vectors and append
+// the candidates directly (dense_threshold).  Blocks where a stage overflows its
+// LDS, or with more entries per row than a form holds (128, or Dense::kMaxK: 384,
+// 256 and 128 at 64, 32 and 16 elements per lane), take an exact bitwise search
+// over all elements instead.
 constexpr int kMaxCandVec = 128;   // candidate vectors gathered in LDS
 constexpr int kCandMax = 256;      // candidate elements resolved
 

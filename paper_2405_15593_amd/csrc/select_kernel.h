@@ -9,8 +9,8 @@ namespace microadam {
 namespace {
 
 // ---------------------------------------------- denser selections (DENSE)
-// More than about 64 entries per row leave the half-lane maxima too coarse a
-// bound (the vectors above it overflow their LDS, and k > 128 has none), so
+// Rows of more than 58 entries leave the half-lane maxima too coarse a bound
+// (the vectors above it overflow their LDS, and k > 128 has none), so
 // the lower bound L comes from the maxima of all 8-element vectors (the
 // largest 13-bit prefix with at least k of them at or above it), and every
 // lane appends its elements >= L (the candidates, about 1.25 k of them at 5%)
@@ -74,7 +74,11 @@ __device__ __forceinline__ bool dense_threshold(const float (&a)[EPL / 8][8], co
   }
   if (C > (uint32_t)kCand || C < (uint32_t)kq) return false;
   {
-    // elements below L go to the lane's sink: no branch per element
+    // Elements below L go to the lane's sink: no branch per element.  A lane
+    // starts at most at C <= kCand and appends at most EPL elements, so that even
+    // if this compare and the count's treated a NaN differently no write would
+    // leave the list and the wave's sinks after it.
+    static_assert(EPL <= kWave, "a lane's appends past the list end among the sinks");
     const float L2 = opaque_f(L);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
