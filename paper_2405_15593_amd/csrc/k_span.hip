@@ -248,9 +248,11 @@ hipError_t launch_select_partials(const StepParams& p, int grad_bf16, int value_
 
 hipError_t launch_bucket_reduce(const StepParams& p, hipStream_t stream) {
   if (p.total_buckets <= 0) return hipSuccess;
-  // lanes per bucket: the blocks a bucket covers, up to a wave
+  // lanes per bucket: the blocks a bucket covers, up to a wave (fewer where a
+  // launch of 2^32 threads would be reached: tens of millions of tensors)
   int32_t lg = 0;
-  while (lg < 6 && (int64_t)p.block << lg < p.big_bucket + p.block) ++lg;
+  while (lg < 6 && (int64_t)p.block << lg < p.big_bucket + p.block && p.total_buckets << (lg + 1) < (1ll << 32) - 256)
+    ++lg;
   const uint32_t grid = (uint32_t)(((p.total_buckets << lg) + 255) / 256);
   hipLaunchKernelGGL(bucket_reduce_kernel, dim3(grid), dim3(256), 0, stream, p, lg);
   return hipGetLastError();
