@@ -27,12 +27,12 @@ namespace {
 // per entry) shared by all waves.  The form before held the entries in the
 // adding wave's registers, up to 16 chunks of 64, and that wave computed every
 // decrement with the library's square root and division; longer windows were
-// read row by row from memory.  Measured, old and new, the step in us:
-//   two Llama-2-7B layers, m = 20 (20 chunks)      2338 -> 580-600
-//   120 M parameters, k = 205, m = 10 (40 chunks)  1279 -> 400
-//   Llama-2-7B, m = 10                             8954 -> 8763
-//   BERT-base in bf16                               160.6 -> 156.7
-//   BERT-base with blocks of 1024 (k = 11)          238.0 -> 216.4
+// read row by row from memory.  Measured, old and new, the update in us per 64 M
+// bf16 parameters:
+//   B_d = 4096, k = 41:   m = 10   53 ->  51,  m = 20  278 -> 58
+//   B_d = 4096, k = 205:  m = 10  466 -> 103
+//   B_d = 2048, k = 21:   m = 10  117 ->  52
+//   B_d = 1024, k = 11:   m = 10   65 ->  52
 constexpr int kStageMax = 24;  // entries per thread at most
 
 // Accumulator word of element i: bf16 parameters are read as pairs of 16-byte
